@@ -250,20 +250,20 @@ mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape *shape, in
                           const int32_t *d_block_table, int32_t bt_stride, const void *d_q,
                           void *d_out, mw_stream stream, mw_timing *timing);
 
-/* Prefill with a key-range split for grids too small to fill the stream's
- * CUs (the launches that run 32-position query blocks, two work-groups per
- * CU: a lone prefill on the whole device, a tensor-parallel head shard on a
- * partition).  There the longest causal block (its keys 0 .. r + i) sets the
- * call's time; the split cuts each block's key range into up to 8 equal
- * pieces so that the pieces fill about three rounds of the stream's
- * work-group slots, each piece computes the partial softmax state (reference
- * maximum m, row sum l, unnormalised output) of its keys into the workspace,
- * and a second kernel merges the pieces of every split block with the
- * log-sum-exp identity (the decode combine's merge; Table "tab:theory_cost"
- * fixes every row's key set, so the merged result is the same attention).
- * Without a split to make (a grid that fills the CUs, or blocks of at most
- * 4 key tiles) this is mw_prefill_attn: one launch, workspace unused.  With
- * one, two launches (split, merge), recorded as two kernels in `timing`.
+/* Prefill with split key ranges for grids too small to fill the stream's CUs
+ * with 8-wave work-groups on 256 query rows each (a lone prompt on the whole
+ * device, a tensor-parallel head shard on a partition).  Such a call runs
+ * blocks of 128 rows whose key tiles the two halves of a work-group share,
+ * merged inside it.  Where whole blocks would still leave CUs idle or end
+ * unevenly, each block's key range is also cut into up to 8 equal pieces (the
+ * number by a cost model): each piece computes the partial softmax state
+ * (reference maximum m, row sum l, unnormalised output) of its keys into the
+ * workspace, and a second kernel merges the pieces of every split block with
+ * the log-sum-exp identity (the decode combine's merge; Table
+ * "tab:theory_cost" fixes every row's key set, so the merged result is the same
+ * attention).  Without pieces (a grid that fills the CUs, or blocks of at most
+ * 4 key tiles) this is one launch, workspace unused.  With them, two launches
+ * (split, merge), recorded as two kernels in `timing`.
  * The split depends on the lengths and on the stream's CU count, never on
  * page ids; rounding may differ from mw_prefill_attn in the last bits.
  *

@@ -118,10 +118,10 @@ bool decode_terms(int32_t batch, const int32_t *lens, double out[4]) {
     return true;
 }
 
-// The library's prefill launch on `cus` CUs, from the lengths: its kernel path
-// (0: 8-wave blocks of 64 positions, one work-group per CU; 1: 4-wave blocks
-// of 32 positions, two work-groups per CU, with the key-range split when its
-// plan cuts, as a call with a workspace makes it) and its load-imbalance
+// The modelled prefill launch on `cus` CUs, from the lengths: its path (0:
+// blocks of 64 positions, one work-group per CU; 1: blocks of 32 positions, two
+// per CU, cut into key ranges by model_split; the library's calls take their
+// 256-row and 128-row blocks on the same condition) and its load-imbalance
 // factor: the latest CU's finishing time over the time of the same work spread
 // evenly over the CUs.  The work-groups are taken in dispatch order (grid x
 // fastest, then the sequence) and each goes to the CU slot that frees first,
@@ -135,13 +135,37 @@ struct PrefillLaunch {
     double kappa;
 };
 
+// The key-range split of the modelled launch, in blocks of 32 positions: with
+// fewer blocks than CUs, pieces that give about two work-groups per CU; with
+// fewer than two per CU, long blocks (96 tiles and more) cut in three.
+void model_split(int32_t batch, const int32_t *nl, const int32_t *rl, int64_t heads, int64_t cus, PrefillPlan *pl) {
+    int max_nt = 0;
+    int64_t units = 0;
+    for (int32_t b = 0; b < batch; ++b) {
+        if (nl[b] > 0) max_nt = std::max(max_nt, (rl[b] + nl[b] + 63) / 64);
+        units += (nl[b] + 31) / 32;
+    }
+    units *= heads;
+    if (units == 0) return;
+    int64_t k = 1;
+    if (units < cus)
+        k = std::min<int64_t>(kPrefillMaxPieces, std::max<int64_t>(2, (2 * cus + units - 1) / units));
+    else if (units < 2 * cus && max_nt >= 96)
+        k = 3;
+    if (k == 1) return;
+    pl->piece_tiles = std::max<int>(kPrefillMinPieceTiles, static_cast<int>((max_nt + k - 1) / k));
+    pl->pieces = prefill_pieces(max_nt, pl->piece_tiles, kPrefillMaxPieces);
+}
+
 PrefillLaunch prefill_launch(int32_t batch, const int32_t *nl, const int32_t *rl, int hkv, int group, int64_t cus) {
     PrefillPlan pl;
-    prefill_plan_lengths(batch, nl, hkv, group, cus, true, &pl);
-    if (pl.waves == 4) prefill_split_plan(batch, nl, rl, hkv * group, cus, &pl);
+    // modelled in blocks of 32 or 64 positions of up to four query heads (a
+    // group of 4 fills a block's 128 or 256 rows exactly)
+    const int64_t heads = static_cast<int64_t>(hkv) * ((group + 3) / 4);
+    prefill_plan_lengths(batch, nl, static_cast<int>(heads), 4, cus, true, &pl);
+    if (pl.waves == 4) model_split(batch, nl, rl, heads, cus, &pl);
     const int bm = pl.waves == 4 ? 32 : 64;
     const int per_cu = pl.waves == 4 ? 2 : 1;
-    const int64_t heads = static_cast<int64_t>(pl.hkv) * pl.n_hgroups;
     int64_t max_n = 0;
     for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, nl[b]);
     std::vector<double> work;

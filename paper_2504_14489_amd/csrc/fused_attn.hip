@@ -35,7 +35,7 @@ k_fused_attn(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vp
              // prefill
              const uint16_t *__restrict__ pq, uint16_t *__restrict__ pout, const int32_t *__restrict__ qo_indptr,
              const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ pbt, int pbt_stride, int pgroup,
-             float pscale_log2, int paired, int n_hgroups, int gx, int64_t n_pre,
+             float pscale_log2, int pbatch, int order, int gx, int64_t n_pre,
              // decode
              const uint16_t *__restrict__ dq, uint16_t *__restrict__ dout, const int32_t *__restrict__ seq_lens,
              const int32_t *__restrict__ dbt, int dbt_stride, float *__restrict__ ws_o, float2 *__restrict__ ws_ml,
@@ -48,11 +48,12 @@ k_fused_attn(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vp
     const int64_t p_lo = i * n_pre / total, p_hi = (i + 1) * n_pre / total;
     if (p_hi > p_lo) {
         const int x = static_cast<int>(p_lo % gx), b = static_cast<int>(p_lo / gx);
-        pf::prefill_block<kTableInLds, 8>(kpool, vpool, pq, pout, qo_indptr, prefix_lens, pbt, pbt_stride, hkv, pgroup,
-                                       num_pages, pscale_log2, paired, n_hgroups, x, b,
-                                       reinterpret_cast<uint16_t *>(lds + kPrefillK),
-                                       reinterpret_cast<uint16_t *>(lds + kPrefillV),
-                                       reinterpret_cast<int32_t *>(lds + kPrefillBt));
+        pf::Item item;
+        if (!pf::work_item<256>(qo_indptr, prefix_lens, pbatch, hkv, pgroup, order, x, b, item)) return;
+        pf::prefill_block<kTableInLds, 8>(kpool, vpool, pq, pout, pbt, pbt_stride, hkv, pgroup, num_pages,
+                                          pscale_log2, item, reinterpret_cast<uint16_t *>(lds + kPrefillK),
+                                          reinterpret_cast<uint16_t *>(lds + kPrefillV),
+                                          reinterpret_cast<int32_t *>(lds + kPrefillBt));
     } else {
         const int64_t pair = i - p_hi;
         const int half = threadIdx.x >> 8;
@@ -79,7 +80,7 @@ extern "C" mw_status mw_fused_attn(const mw_prefill_args *pre, const mw_decode_a
     DecodePlan dp;
     st = decode_prepare(dec, 0, &dp, who);  // fixed chunks: a fused work-group's barriers are uniform
     if (st != MW_OK) return st;
-    const int64_t n_pre = pp.gx * pp.batch, n_dec = (dp.units + 1) / 2;
+    const int64_t n_pre = pp.grid_x * pp.grid_y, n_dec = (dp.units + 1) / 2;
     if (n_pre + n_dec > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     st = timing_begin(timing, s);
     if (st != MW_OK) return st;
@@ -90,8 +91,8 @@ extern "C" mw_status mw_fused_attn(const mw_prefill_args *pre, const mw_decode_a
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_pre + n_dec)), dim3(kThreadsFused), 0, s, pool->k,
                            pool->v, pool->desc.num_pages, pp.hkv, static_cast<const uint16_t *>(pre->d_q),
                            static_cast<uint16_t *>(pre->d_out), pre->d_qo_indptr, pre->d_prefix_lens,
-                           pre->d_block_table, pre->bt_stride, pp.group, pp.scale_log2, pp.paired, pp.n_hgroups,
-                           static_cast<int>(pp.gx > 0 ? pp.gx : 1), n_pre, static_cast<const uint16_t *>(dec->d_q),
+                           pre->d_block_table, pre->bt_stride, pp.group, pp.scale_log2, pp.batch, pp.order,
+                           static_cast<int>(pp.grid_x > 0 ? pp.grid_x : 1), n_pre, static_cast<const uint16_t *>(dec->d_q),
                            static_cast<uint16_t *>(dec->d_out), dec->d_seq_lens, dec->d_block_table, dec->bt_stride,
                            reinterpret_cast<float *>(ws), reinterpret_cast<float2 *>(ws + dp.off_ml),
                            reinterpret_cast<int32_t *>(ws + dp.off_meta), dec->batch, dp.group, dp.scale_log2,

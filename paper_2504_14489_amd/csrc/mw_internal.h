@@ -24,20 +24,22 @@ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 // Key-range split of the prefill query blocks of the 4-wave kernel: a block
 // whose causal key range spans nt tiles of 64 keys is cut into this many
 // pieces, piece i covering tiles [i nt / k, (i + 1) nt / k).  With
-// piece_tiles >= 4 every cut lies at least two tiles before the block's end,
+// piece_tiles >= 4 every cut lies at least three tiles before the block's end,
 // so the first tile of every piece holds a key that every query of the block
-// sees (a block's last two tiles hold its diagonal).
+// sees (a block of at most 128 positions has its diagonal in its last three
+// tiles).
 constexpr int kPrefillMaxPieces = 8;
 constexpr int kPrefillMinPieceTiles = 4;
 __host__ __device__ inline int prefill_pieces(int nt, int piece_tiles, int max_pieces) {
     const int k = (nt + piece_tiles - 1) / piece_tiles;
     return k < 1 ? 1 : (k > max_pieces ? max_pieces : k);
 }
-// Key tiles (64 keys) of the 32-position query block q of a sequence with
-// prefix r and n new tokens.
-__host__ __device__ inline int prefill_block_tiles(int r, int n, int q) {
-    const int end = 32 * q + 32 < n ? 32 * q + 32 : n;
-    return (r + end + 63) / 64;
+// Key tiles (64 keys) of query block q of a sequence with prefix r and n new
+// tokens: blocks of `block_rows` rows of n x group queries (by default 32
+// positions).
+__host__ __device__ inline int prefill_block_tiles(int r, int n, int q, int block_rows = 32, int group = 1) {
+    const int end = (q + 1) * block_rows < n * group ? (q + 1) * block_rows : n * group;
+    return (r + (end + group - 1) / group + 63) / 64;
 }
 
 // Number of CUs a stream's kernels may run on (its CU mask; all CUs of the
@@ -117,10 +119,14 @@ mw_status decode_combine_launch(const mw_decode_args *a, const DecodePlan &p, hi
 
 // Checked launch parameters of one prefill call.
 struct PrefillPlan {
-    int hkv, group, n_hgroups, paired;
-    int waves;            // 8 (64-position query blocks) or 4 (32-position blocks)
-    int64_t gx;           // work-groups per sequence (grid x); 0: nothing to do
+    int hkv, group, paired;
+    int waves;            // 8 (256-row query blocks) or 4 (128-row blocks)
+    int64_t gx;           // most work-groups of a sequence; 0: nothing to do
     int batch;
+    // the launch: grid and order of the query blocks (prefill_block.h)
+    int64_t grid_x;
+    int grid_y, order;
+    int64_t blocks;       // query blocks of the batch, per kv head
     bool table_in_lds;    // every block-table entry a work-group needs fits its LDS copy
     float scale_log2;
     // key-range split (4-wave blocks only; planned by prefill_split_plan)
@@ -134,7 +140,7 @@ struct PrefillPlan {
 // on it).
 mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who);
 // The launch plan of a prefill call from its lengths alone (no validation):
-// waves, pairing and grid width for a stream of `cus` CUs; used by
+// waves, pairing, grid and order for a stream of `cus` CUs; used by
 // prefill_prepare and by the latency predictor, which simulates the launch.
 void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int group, int64_t cus,
                           bool allow_small, PrefillPlan *p);

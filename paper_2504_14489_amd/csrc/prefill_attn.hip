@@ -16,75 +16,100 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1)
 k_prefill_attn(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
                const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
                const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
-               const int32_t *__restrict__ bt, int bt_stride, int hkv, int group, int num_pages,
-               float scale_log2, int paired, int n_hgroups) {
+               const int32_t *__restrict__ bt, int bt_stride, int batch, int hkv, int group, int num_pages,
+               float scale_log2, int order) {
     __shared__ __attribute__((aligned(1024))) uint16_t s_k[2 * TILE];
     __shared__ __attribute__((aligned(1024))) uint16_t s_v[2 * TILE];
     __shared__ int32_t s_bt[kBtCache];
-    prefill_block<kTableInLds, NW>(kpool, vpool, q, out, qo_indptr, prefix_lens, bt, bt_stride, hkv, group, num_pages,
-                               scale_log2, paired, n_hgroups, blockIdx.x, blockIdx.y, s_k, s_v, s_bt);
+    Item item;
+    if (!work_item<32 * NW>(qo_indptr, prefix_lens, batch, hkv, group, order, blockIdx.x, blockIdx.y, item))
+        return;
+    prefill_block<kTableInLds, NW>(kpool, vpool, q, out, bt, bt_stride, hkv, group, num_pages, scale_log2, item, s_k,
+                                   s_v, s_bt);
 }
 
-// Key-range split of small grids (4-wave blocks): work-group (x, b) runs
-// piece x % max_pieces of block unit x / max_pieces (nothing when the block
-// has fewer pieces), so the pieces of a block are dispatched together,
-// heaviest blocks first.
-template <bool kTableInLds>
-__global__ void __launch_bounds__(256, 2)
-k_prefill_split(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
-                const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
-                const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
-                const int32_t *__restrict__ bt, int bt_stride, int hkv, int group, int num_pages,
-                float scale_log2, int n_hgroups, float *__restrict__ ws_o, float2 *__restrict__ ws_ml,
-                int64_t rows, int piece_tiles, int max_pieces) {
-    __shared__ __attribute__((aligned(1024))) uint16_t s_k[2 * TILE];
-    __shared__ __attribute__((aligned(1024))) uint16_t s_v[2 * TILE];
+// Launches of fewer pairs of 256-row blocks than CUs, through the entry point
+// that may split key ranges: 128-row blocks whose keys the two wave groups
+// share (kDual), one work-group per CU.  With kSplit, work-group (x, y) runs
+// piece x % max_pieces of block unit x / max_pieces (nothing when the block has
+// fewer pieces), so the pieces of a block are dispatched together, heaviest
+// blocks first.
+template <bool kTableInLds, bool kSplit>
+__global__ void __launch_bounds__(512, 1)
+k_prefill_dual(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
+               const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
+               const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
+               const int32_t *__restrict__ bt, int bt_stride, int batch, int hkv, int group, int num_pages,
+               float scale_log2, int order, float *__restrict__ ws_o, float2 *__restrict__ ws_ml,
+               int64_t rows, int piece_tiles, int max_pieces) {
+    __shared__ __attribute__((aligned(1024))) uint16_t s_k[4 * TILE];
+    __shared__ __attribute__((aligned(1024))) uint16_t s_v[4 * TILE];
     __shared__ int32_t s_bt[kBtCache];
-    const int unit = static_cast<int>(blockIdx.x) / max_pieces;
-    const SplitOut sp{ws_o, ws_ml, rows, piece_tiles, max_pieces, static_cast<int>(blockIdx.x) % max_pieces};
-    prefill_block<kTableInLds, 4, true>(kpool, vpool, q, out, qo_indptr, prefix_lens, bt, bt_stride, hkv, group,
-                                        num_pages, scale_log2, 0, n_hgroups, unit, blockIdx.y, s_k, s_v, s_bt, sp);
+    const int unit = kSplit ? static_cast<int>(blockIdx.x) / max_pieces : static_cast<int>(blockIdx.x);
+    const SplitOut sp{ws_o, ws_ml, rows, piece_tiles, max_pieces, static_cast<int>(blockIdx.x) - unit * max_pieces};
+    Item item;
+    if (!work_item<128>(qo_indptr, prefix_lens, batch, hkv, group, order, unit, blockIdx.y, item)) return;
+    prefill_block<kTableInLds, 8, true, kSplit>(kpool, vpool, q, out, bt, bt_stride, hkv, group, num_pages, scale_log2,
+                                                item, s_k, s_v, s_bt, sp);
 }
 
-// Merge of the pieces of every split block: work-group (q * hq + h, b) takes
-// the 32 rows of block q of sequence b for query head h (8 threads per row,
-// 16 dims each): with M the largest reference maximum of the pieces,
+// Merge of the pieces of every split block: work-group (x, b) takes 32 of the
+// n x hq output rows of sequence b (8 threads per row, 16 dims each): with M
+// the largest reference maximum of the pieces,
 // O = sum_i 2^(m_i - M) O~_i / sum_i 2^(m_i - M) l_i, written as bf16.
-// Blocks with one piece were written by the split kernel itself.
+// Rows of blocks with one piece were written by the split kernel itself.
 __global__ void __launch_bounds__(256)
 k_prefill_merge(const float *__restrict__ ws_o, const float2 *__restrict__ ws_ml, uint16_t *__restrict__ out,
-                const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens, int hq,
+                const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens, int hq, int group,
                 int64_t rows, int piece_tiles, int max_pieces) {
     const int b = blockIdx.y;
-    const int qb = blockIdx.x / hq, h = blockIdx.x % hq;
     const int row0 = qo_indptr[b];
     const int n = qo_indptr[b + 1] - row0;
-    if (32 * qb >= n) return;
-    const int k = prefill_pieces(prefill_block_tiles(prefix_lens[b], n, qb), piece_tiles, max_pieces);
-    if (k < 2) return;
-    const int i = 32 * qb + static_cast<int>(threadIdx.x >> 3);
+    const unsigned at = 32u * blockIdx.x + (threadIdx.x >> 3);
+    const int i = static_cast<int>(at / static_cast<unsigned>(hq)), h = static_cast<int>(at) - i * hq;
     if (i >= n) return;
+    const int k = prefill_pieces(prefill_block_tiles(prefix_lens[b], n, (i * group + h % group) / 128, 128, group),
+                                 piece_tiles, max_pieces);
+    if (k < 2) return;
     const int d0 = 16 * (threadIdx.x & 7);
     const size_t row = static_cast<size_t>(row0 + i) * hq + h;
     const size_t stride = static_cast<size_t>(rows) * hq;  // one piece's slot
+    // every piece's (m, l) and four pieces' O~ are requested together (one
+    // piece at a time, 4 pieces of 2048 rows x 8 heads took 8.6 us)
+    float2 ml[kPrefillMaxPieces];
+#pragma unroll
+    for (int p = 0; p < kPrefillMaxPieces; ++p)
+        ml[p] = p < k ? ws_ml[p * stride + row] : make_float2(-INFINITY, 0.f);
     float m = -INFINITY;
-    for (int p = 0; p < k; ++p) m = fmaxf(m, ws_ml[p * stride + row].x);
+#pragma unroll
+    for (int p = 0; p < kPrefillMaxPieces; ++p) m = fmaxf(m, ml[p].x);
     float l = 0.f, o[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[e] = 0.f;
-    for (int p = 0; p < k; ++p) {
-        const float2 ml = ws_ml[p * stride + row];
-        if (!(ml.y > 0.f)) continue;  // no keys: contributes nothing
-        const float w = exp2f(ml.x - m);
-        l += w * ml.y;
-        const float4 *src = reinterpret_cast<const float4 *>(ws_o + (p * stride + row) * kHeadDim + d0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float4 v = src[e];
-            o[4 * e + 0] += w * v.x;
-            o[4 * e + 1] += w * v.y;
-            o[4 * e + 2] += w * v.z;
-            o[4 * e + 3] += w * v.w;
+    for (int p0 = 0; p0 < kPrefillMaxPieces; p0 += 4) {
+        if (p0 >= k) break;
+        float4 v[4][4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float4 *src = reinterpret_cast<const float4 *>(
+                ws_o + ((p0 + p < k ? p0 + p : 0) * stride + row) * kHeadDim + d0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[p][e] = src[e];
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            // a piece without keys contributes nothing (nor does one past k)
+            const bool in = ml[p0 + p].y > 0.f;
+            const float w = in ? exp2f(ml[p0 + p].x - m) : 0.f;
+            l += w * ml[p0 + p].y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                o[4 * e + 0] += in ? w * v[p][e].x : 0.f;
+                o[4 * e + 1] += in ? w * v[p][e].y : 0.f;
+                o[4 * e + 2] += in ? w * v[p][e].z : 0.f;
+                o[4 * e + 3] += in ? w * v[p][e].w : 0.f;
+            }
         }
     }
     const float inv = 1.f / l;
@@ -95,6 +120,10 @@ k_prefill_merge(const float *__restrict__ ws_o, const float2 *__restrict__ ws_ml
     dst[0] = make_uint4(packed[0], packed[1], packed[2], packed[3]);
     dst[1] = make_uint4(packed[4], packed[5], packed[6], packed[7]);
 }
+
+// Sequences of a call whose blocks are ordered over the whole batch (one lane
+// of a wave each).
+constexpr int kMaxSorted = 64;
 
 }  // namespace
 
@@ -107,14 +136,19 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     p->split_bytes = 0;
     p->rows = 0;
     int max_nt = 0;
-    int64_t units = 0;  // 32-position query blocks x kv heads x head groups
+    int64_t units = 0, tiles = 0;  // 128-row query blocks x kv heads, and their key tiles
     for (int32_t b = 0; b < batch; ++b) {
         const int n = h_new_lens[b], r = h_prefix_lens[b];
         p->rows += n;
-        if (n > 0) max_nt = std::max(max_nt, prefill_block_tiles(r, n, (n - 1) / 32));
-        units += (n + 31) / 32;
+        const int64_t blocks = (static_cast<int64_t>(n) * p->group + 127) / 128;
+        if (blocks == 0) continue;
+        const int first = prefill_block_tiles(r, n, 0, 128, p->group), last = (r + n + 63) / 64;
+        max_nt = std::max(max_nt, last);
+        units += blocks;
+        tiles += blocks * (first + last) / 2;
     }
-    units *= static_cast<int64_t>(p->hkv) * p->n_hgroups;
+    units *= p->hkv;
+    tiles *= p->hkv;
     if (p->waves != 4 || units == 0) return;
     const auto bytes_for = [&](int pieces) {
         return pieces > 1 ? static_cast<size_t>(pieces) * p->rows * hq * (kHeadDim * 4 + 8) : 0;
@@ -125,31 +159,43 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
         p->split_bytes = bytes_for(p->pieces);
         return;
     }
-    // Measured on 2048-token chunks of a one-kv-head shard and of an 8-kv-head
-    // layer (piece lengths swept 4..48 tiles): with fewer blocks than CUs,
-    // pieces that give about two work-groups per CU (the longest block cut in
-    // 2C / units); with fewer than two per CU, long blocks (96 tiles and more)
-    // cut in three, which evens out the CUs holding one block and those
-    // holding two; otherwise (short blocks, or a grid of two blocks per CU) the
-    // merge pass costs more than the cut saves.
-    int k = 1;
-    if (units < cus)
-        k = static_cast<int>(std::min<int64_t>(kPrefillMaxPieces, std::max<int64_t>(2, (2 * cus + units - 1) / units)));
-    else if (units < 2 * cus && max_nt >= 96)
-        k = 3;
-    const int best_pt = k > 1 ? std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k) : 0;
+    // The cheapest number of pieces of the longest block, in microseconds.  A
+    // work-group takes 1.65 us per two tiles and 6 us around them (measured
+    // with clock stamps on the whole GPU: 1.60-1.72 and 5.4-6.1 over a 2048-
+    // and a 1000-token chunk and a one-kv-head shard).  Up to one work-group
+    // per CU the call lasts as long as the longest piece, past that as the
+    // work's even share and half a piece.  The merge is a launch (2 us) and a
+    // pass over the partials, written and read at about 4 TB/s.  With fewer
+    // blocks than CUs, or with fewer than two per CU and blocks of 96 tiles or
+    // more, whole blocks always lose (or tie) and are not considered; two
+    // blocks per CU and more even out by themselves and are never cut.
+    const double kTwoTiles = 1.65, kAround = 6.0, kMergeLaunch = 2.0, kMergeBytesPerUs = 4e6;
+    const bool must_cut = units < cus || (units < 2 * cus && max_nt >= 96);
+    double best = INFINITY;
+    int best_pt = 0;
+    for (int k = must_cut ? 2 : 1; k <= (units < 2 * cus ? kPrefillMaxPieces : 1); ++k) {
+        const int pt = std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k);
+        const double longest = kAround + kTwoTiles * ((pt + 1) / 2);
+        double us = longest;
+        if (units * k > cus)
+            us = static_cast<double>(kAround * units * k + kTwoTiles * tiles / 2) / cus + 0.5 * longest;
+        if (k > 1) us += kMergeLaunch + 2.0 * bytes_for(k) / kMergeBytesPerUs;
+        if (us < best) {
+            best = us;
+            best_pt = k > 1 ? pt : 0;
+        }
+    }
     if (best_pt == 0) return;
     p->piece_tiles = best_pt;
     p->pieces = prefill_pieces(max_nt, best_pt, kPrefillMaxPieces);
     p->split_bytes = bytes_for(p->pieces);
 }
 
-
-
-// Pairs of query blocks of bm positions over a batch's sequences.
-static int64_t prefill_pairs(int32_t batch, const int32_t *h_new_lens, int64_t bm) {
+// Pairs of query blocks of `block_rows` rows over a batch's sequences.
+static int64_t prefill_pairs(int32_t batch, const int32_t *h_new_lens, int group, int64_t block_rows) {
     int64_t n_pairs = 0;
-    for (int32_t b = 0; b < batch; ++b) n_pairs += ((h_new_lens[b] + bm - 1) / bm + 1) / 2;
+    for (int32_t b = 0; b < batch; ++b)
+        n_pairs += ((static_cast<int64_t>(h_new_lens[b]) * group + block_rows - 1) / block_rows + 1) / 2;
     return n_pairs;
 }
 
@@ -184,7 +230,7 @@ mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_smal
                          allow_small, p);
     p->table_in_lds = max_pages <= kBtCache;
     p->scale_log2 = shape->scale * kLog2e;
-    if (p->gx > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
+    if (p->grid_x > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     return MW_OK;
 }
 
@@ -192,12 +238,13 @@ void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int
                           bool allow_small, PrefillPlan *p) {
     p->hkv = hkv;
     p->group = group;
-    p->n_hgroups = (group + 3) / 4;
     p->batch = batch;
     p->table_in_lds = true;
     p->scale_log2 = 0.f;
     p->paired = 0;
-    p->gx = 0;
+    p->gx = p->grid_x = p->blocks = 0;
+    p->grid_y = 1;
+    p->order = kPerSequence;
     p->pieces = 1;
     p->piece_tiles = 0;
     p->rows = 0;
@@ -206,24 +253,36 @@ void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int
     int64_t max_n = 0;
     for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, h_new_lens[b]);
     if (max_n == 0) return;
-    auto pairs_of = [&](int64_t bm) { return prefill_pairs(batch, h_new_lens, bm) * p->hkv * p->n_hgroups; };
-    // Eight waves (64-position blocks, one work-group per CU) unless their pairs
-    // would not even give every CU one: then four waves (32-position blocks,
+    auto pairs_of = [&](int64_t rows) { return prefill_pairs(batch, h_new_lens, group, rows) * hkv; };
+    // Eight waves (256-row blocks, one work-group per CU) unless their pairs
+    // would not even give every CU one: then four waves (128-row blocks,
     // two work-groups per CU), which doubles the work-groups.
-    int64_t bm = BM, slots = cus;
-    if (allow_small && pairs_of(BM) < cus) {
+    int64_t rows = 256, slots = cus;
+    if (allow_small && pairs_of(rows) < cus) {
         p->waves = 4;
-        bm = BM / 2;
+        rows = 128;
         slots = 2 * cus;
     }
     // Pair blocks only when the pairs fill whole rounds of the work-group slots
     // of the stream's CUs: equal-cost pairs then finish together.  Otherwise
     // single blocks, heaviest first, fill the last round better.
-    const int64_t max_qblocks = (max_n + bm - 1) / bm;
-    const int64_t n_pairs = pairs_of(bm);
+    const int64_t max_blocks = (max_n * group + rows - 1) / rows;
+    const int64_t n_pairs = pairs_of(rows);
     const int64_t rounds = (n_pairs + slots - 1) / slots;
     p->paired = n_pairs >= slots && rounds * slots * 20 <= n_pairs * 21;
-    p->gx = (p->paired ? (max_qblocks + 1) / 2 : max_qblocks) * p->hkv * p->n_hgroups;
+    p->gx = (p->paired ? (max_blocks + 1) / 2 : max_blocks) * hkv;
+    for (int32_t b = 0; b < batch; ++b) p->blocks += (static_cast<int64_t>(h_new_lens[b]) * group + rows - 1) / rows;
+    // Up to 64 sequences: blocks ordered over the whole batch (a sequence at a
+    // time leaves the last one's long blocks to the end of the launch, and
+    // gives every sequence as many work-groups as the longest needs)
+    if (batch > 1 && batch <= kMaxSorted) {
+        p->order = kSorted;
+        p->grid_x = p->blocks * hkv;
+    } else {
+        p->order = p->paired ? kPairs : kPerSequence;
+        p->grid_x = p->gx;
+        p->grid_y = batch;
+    }
 }
 
 }  // namespace mw
@@ -243,13 +302,13 @@ extern "C" mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape
     if (st != MW_OK) return st;
     st = timing_begin(timing, s);
     if (st != MW_OK) return st;
-    if (pl.gx > 0) {
+    if (pl.grid_x > 0) {
         auto kernel = pl.waves == 4 ? (pl.table_in_lds ? k_prefill_attn<true, 4> : k_prefill_attn<false, 4>)
                                     : (pl.table_in_lds ? k_prefill_attn<true, 8> : k_prefill_attn<false, 8>);
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.gx), batch), dim3(64 * pl.waves), 0, s, pool->k,
-                           pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out), d_qo_indptr,
-                           d_prefix_lens, d_block_table, bt_stride, pl.hkv, pl.group, pool->desc.num_pages,
-                           pl.scale_log2, pl.paired, pl.n_hgroups);
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.grid_x), pl.grid_y), dim3(64 * pl.waves), 0, s,
+                           pool->k, pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out),
+                           d_qo_indptr, d_prefix_lens, d_block_table, bt_stride, batch, pl.hkv, pl.group,
+                           pool->desc.num_pages, pl.scale_log2, pl.order);
         st = check_launch("k_prefill_attn");
         if (st != MW_OK) return st;
     }
@@ -273,10 +332,9 @@ extern "C" mw_status mw_prefill_workspace_size(const mw_attn_shape *shape, int32
     PrefillPlan pl{};
     pl.hkv = shape->num_kv_heads;
     pl.group = shape->num_q_heads / pl.hkv;
-    pl.n_hgroups = (pl.group + 3) / 4;
     // the split runs where the launch takes 4-wave blocks (as in prefill_prepare);
     // without a CU count, size for any stream
-    pl.waves = num_cus == 0 || prefill_pairs(batch, h_new_lens, BM) * pl.hkv * pl.n_hgroups < num_cus ? 4 : 8;
+    pl.waves = num_cus == 0 || prefill_pairs(batch, h_new_lens, pl.group, 256) * pl.hkv < num_cus ? 4 : 8;
     prefill_split_plan(batch, h_new_lens, h_prefix_lens, shape->num_q_heads, num_cus, &pl);
     *bytes = pl.split_bytes;
     return MW_OK;
@@ -297,16 +355,19 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
     const int64_t cus = stream_cus(s);
     mw_status st = prefill_prepare(&a, cus, true, &pl, who);
     if (st != MW_OK) return st;
+    if (pl.waves == 8 || pl.gx == 0)
+        return mw_prefill_attn(pool, shape, batch, h_new_lens, h_prefix_lens, d_qo_indptr, d_prefix_lens,
+                               d_block_table, bt_stride, d_q, d_out, stream, timing);
     prefill_split_plan(batch, h_new_lens, h_prefix_lens, shape->num_q_heads, cus, &pl);
-    if (pl.pieces < 2 || pl.gx == 0) return mw_prefill_attn(pool, shape, batch, h_new_lens, h_prefix_lens,
-                                                            d_qo_indptr, d_prefix_lens, d_block_table, bt_stride,
-                                                            d_q, d_out, stream, timing);
-    if (!d_workspace || !aligned16(d_workspace) || workspace_bytes < pl.split_bytes)
+    const bool cut = pl.pieces > 1;
+    if (cut && (!d_workspace || !aligned16(d_workspace) || workspace_bytes < pl.split_bytes))
         return fail(MW_ERR_INVALID_ARG, "%s: the split needs a 16-byte aligned workspace of %zu bytes (got %zu)",
                     who, pl.split_bytes, workspace_bytes);
-    int max_n = 0;
-    for (int32_t b = 0; b < batch; ++b) max_n = h_new_lens[b] > max_n ? h_new_lens[b] : max_n;
-    const int64_t gx = static_cast<int64_t>((max_n + 31) / 32) * pl.hkv * pl.n_hgroups;  // single blocks
+    int64_t max_n = 0;
+    for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, h_new_lens[b]);
+    // single blocks, over the whole batch or a sequence at a time
+    const int64_t gx = (pl.order == kSorted ? pl.blocks : (max_n * pl.group + 127) / 128) * pl.hkv;
+    const int order = pl.order == kSorted ? kSorted : kPerSequence;
     if (gx * pl.pieces > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     st = timing_begin(timing, s);
     if (st != MW_OK) return st;
@@ -314,19 +375,24 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
     float2 *ws_ml = reinterpret_cast<float2 *>(static_cast<char *>(d_workspace) +
                                                static_cast<size_t>(pl.pieces) * pl.rows * shape->num_q_heads *
                                                    kHeadDim * 4);
-    auto kernel = pl.table_in_lds ? k_prefill_split<true> : k_prefill_split<false>;
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gx * pl.pieces), batch), dim3(256), 0, s, pool->k,
+    auto kernel = cut ? (pl.table_in_lds ? k_prefill_dual<true, true> : k_prefill_dual<false, true>)
+                      : (pl.table_in_lds ? k_prefill_dual<true, false> : k_prefill_dual<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gx * pl.pieces), pl.grid_y), dim3(512), 0, s, pool->k,
                        pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out), d_qo_indptr,
-                       d_prefix_lens, d_block_table, bt_stride, pl.hkv, pl.group, pool->desc.num_pages, pl.scale_log2,
-                       pl.n_hgroups, ws_o, ws_ml, pl.rows, pl.piece_tiles, pl.pieces);
-    st = check_launch("k_prefill_split");
+                       d_prefix_lens, d_block_table, bt_stride, batch, pl.hkv, pl.group, pool->desc.num_pages,
+                       pl.scale_log2, order, ws_o, ws_ml, pl.rows, pl.piece_tiles, pl.pieces);
+    st = check_launch("k_prefill_dual");
     if (st != MW_OK) return st;
     st = timing_kernel_done(timing, s);
     if (st != MW_OK) return st;
-    const int64_t gm = static_cast<int64_t>((max_n + 31) / 32) * shape->num_q_heads;
+    if (!cut) {
+        timing_end(timing);
+        return MW_OK;
+    }
+    const int64_t gm = (max_n * shape->num_q_heads + 31) / 32;
     hipLaunchKernelGGL(k_prefill_merge, dim3(static_cast<unsigned>(gm), batch), dim3(256), 0, s, ws_o, ws_ml,
-                       static_cast<uint16_t *>(d_out), d_qo_indptr, d_prefix_lens, shape->num_q_heads, pl.rows,
-                       pl.piece_tiles, pl.pieces);
+                       static_cast<uint16_t *>(d_out), d_qo_indptr, d_prefix_lens, shape->num_q_heads,
+                       pl.group, pl.rows, pl.piece_tiles, pl.pieces);
     st = check_launch("k_prefill_merge");
     if (st != MW_OK) return st;
     st = timing_kernel_done(timing, s);

@@ -5,21 +5,35 @@
 // "tab:theory_cost": O(n d^2 + L n d) with L = r + n), so both contractions
 // run on the bf16 matrix cores (fp32 accumulate).
 //
-// Work-group = 8 waves; a query block = 64 query positions x 4 query heads of
-// one kv head; wave w owns head (w % 4) of the group and positions
-// 32*(w / 4) .. +31 of the block, so every K/V tile staged in LDS serves
-// 4 heads x 64 positions.  Each work-group processes two blocks of the same
-// heads, block nqb-1-i and block i: causal blocks grow linearly with the block
-// index, so all pairs cost about the same and the grid has no long tail.
+// The queries of a (sequence, kv head) are its n positions x `group` query
+// heads, laid end to end as rows position * group + head.  A query block is
+// 256 consecutive rows (8 waves; 128 with 4), wave w its rows 32w .. 32w + 31,
+// so every K/V tile staged in LDS serves all of them whatever the group: 64
+// positions of a group of 4, 256 of a group of 1, 16 of a group of 16.  (Four
+// waves of four heads each, the earlier layout, left 3 of 4 waves idle with
+// one query head per kv head: a 1000-token chunk over 1003 cached tokens with
+// 32 query and 32 kv heads took 76 us.)  Which block a work-group runs is the
+// kernel's choice (work_item below); it may run two, one after the other.
 // Each wave's state (Q^T, S, P, O) stays in registers.
 //
-// Per key tile t (all waves, one work-group barrier per tile):
+// Per key tile t of a wave:
 //     S(t)^T = K(t) Q^T;  mask, online softmax of S(t) -> P(t) (bf16);
 //     O^T += V(t)^T P(t)^T
+// Three bodies share these steps: 8 waves on 256 rows, two wave groups half a
+// period apart on the same tiles; kDual, 8 waves on 128 rows, the two groups on
+// alternate tiles, each with its own buffers; and 4 waves on 128 rows, two
+// work-groups per CU.  The first needs the fewest K/V loads per flop.  The
+// second halves a block's time when there are too few blocks for the CUs: a
+// 4-wave work-group alone on its CU takes 1.4 us per tile whether or not
+// another one shares the CU's matrix cores, so the longest block of a
+// 2048-token prompt (32 tiles) bounded the launch at 46 us of a 54 us call; dual
+// blocks take 1.62 us per two tiles (1325 TFLOP/s over 256 CUs, the rate of a
+// 16384^3 library product) and the call 46 us.  The third keeps the plain
+// entry point's results the same bits on any CU count (the groups' merge of
+// the second reorders sums).
 // Key tiles of 64 keys = 4 pages go from HBM straight into LDS with the direct
-// buffer-to-LDS loads, double-buffered: the loads of tile t+1 are issued
-// between the MFMAs of S(t) and waited for at the end of tile t; the first
-// tile of a block is requested before Q and the block-table copy are read.
+// buffer-to-LDS loads, double-buffered; the first tile of a block is requested
+// before Q and the block-table copy are waited for.
 // Rows are 256 B with their 16-byte chunks permuted by XOR with
 // swz(r) = 4(r%4) ^ (r/4)%4, which makes both the 16-byte K operand reads and
 // the transposing V reads bank-conflict free; the permutation is applied on
@@ -54,7 +68,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int BM = 64;                       // query positions per 8-wave work-group
 constexpr int BN = 64;                       // keys per tile
 constexpr int ROW = kHeadDim;                // tile row = one key, 128 bf16 (256 B)
 constexpr int TILE = BN * ROW;               // one K or V tile, bf16 elements
@@ -123,56 +136,137 @@ __device__ inline void wg_barrier() {
     asm volatile("" ::: "memory");
 }
 
+// Inclusive scan over the wave's lanes: lane i receives the sum of x over
+// lanes 0 .. i (lane 63 the total).
+__device__ inline int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// The query block(s) one work-group runs: block blk, then blk2 if >= 0, of
+// sequence b (first row row0 of Q, n new tokens over a prefix of r) and kv
+// head kvh.
+struct Item {
+    int b, kvh, row0, n, r, blk, blk2;
+};
+
+// How the work-groups of a launch are mapped to query blocks.  x counts kv
+// heads fastest: work-groups go round-robin over the 8 XCDs, so with 8 kv heads
+// each XCD's L2 holds the K/V of one.  j = x / hkv is then:
+//   kPerSequence  the j-th heaviest block of sequence blockIdx.y
+//   kPairs        blocks nqb-1-j and j of sequence blockIdx.y (equal cost)
+//   kSorted       the j-th heaviest block of the whole batch (at most 64
+//                 sequences): the blocks of one call are dispatched longest
+//                 first whatever their sequence, and no work-group is empty
+enum { kPerSequence = 0, kPairs = 1, kSorted = 2 };
+
+// Fills `it` for work-group (x, y); false if there is no block for it.
+// kBR: query rows per block.  Uniform over the work-group.
+template <int kBR>
+__device__ __forceinline__ bool work_item(const int32_t *__restrict__ qo_indptr,
+                                          const int32_t *__restrict__ prefix_lens, int batch, int hkv, int group,
+                                          int order, int x, int y, Item &it) {
+    int j = x / hkv;
+    it.kvh = x - j * hkv;
+    it.blk2 = -1;
+    if (order == kSorted && batch > 1) {
+        // lane i: sequence i.  A block of e rows' end reads r + ceil(e / group)
+        // keys, so it has at least T tiles of 64 when e > (64 (T - 1) - r) group:
+        // the last blocks of the sequence, counted without a division.
+        const int lane = threadIdx.x & 63;
+        const bool in = lane < batch;
+        const int first = in ? qo_indptr[lane] : 0;
+        const int n = in ? qo_indptr[lane + 1] - first : 0;
+        const int r = in ? prefix_lens[lane] : 0;
+        const int nqb = (n * group + kBR - 1) / kBR;
+        auto at_least = [&](int t) __attribute__((always_inline)) {  // blocks of t tiles or more
+            const int c = BN * (t - 1) - r;
+            return c < 0 ? nqb : c >= n ? 0 : nqb - static_cast<int>(static_cast<unsigned>(c * group) / kBR);
+        };
+        auto total = [&](int v) __attribute__((always_inline)) {
+            return __builtin_amdgcn_readlane(wave_scan(v), 63);
+        };
+        if (j >= total(nqb)) return false;
+        // the j-th heaviest block has t tiles, t the largest with more than j
+        // blocks of t or more
+        int t = 1, step = 1;
+        while (total(at_least(t + step)) > j) step <<= 1;
+        for (; step > 0; step >>= 1)
+            if (total(at_least(t + step)) > j) t += step;
+        const int above = at_least(t + 1), same = at_least(t) - above;
+        j -= total(above);
+        const int incl = wave_scan(same);
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(j >= incl - same && j < incl);
+        if (!hit) return false;
+        const int src = __builtin_ctzll(hit);
+        it.b = src;
+        it.blk = __builtin_amdgcn_readlane(nqb - above - 1 + incl - same, src) - j;
+        it.row0 = __builtin_amdgcn_readlane(first, src);
+        it.n = __builtin_amdgcn_readlane(n, src);
+        it.r = __builtin_amdgcn_readlane(r, src);
+        return true;
+    }
+    it.b = y;
+    it.row0 = qo_indptr[y];
+    it.n = qo_indptr[y + 1] - it.row0;
+    it.r = prefix_lens[y];
+    const int nqb = (it.n * group + kBR - 1) / kBR;
+    if (j >= (order == kPairs ? (nqb + 1) / 2 : nqb)) return false;
+    it.blk = nqb - 1 - j;
+    if (order == kPairs && j != it.blk) it.blk2 = j;
+    return true;
+}
+
 // kTableInLds: every block-table entry the work-group needs fits the LDS copy.
 // The other instantiation reads entries past it with scalar loads, which makes
 // the compiler wait for all outstanding LDS reads wherever it needs one.
-// NW: waves per work-group.  8 (query blocks of 64 positions; waves w and
-// w+4 share a SIMD) or 4 (blocks of 32 positions, two work-groups per CU):
+// NW: waves per work-group.  8 (query blocks of 256 rows; waves w and
+// w+4 share a SIMD) or 4 (blocks of 128 rows, two work-groups per CU):
 // the same per-wave work, for grids that would leave CUs idle with 8.
-// kSplit (4 waves only): the work-group computes piece sp.piece of its query
+// kDual (8 waves): a block of 128 rows run by both wave groups, group 0 on the
+// key tiles 0, 2, 4 .. and group 1 on 1, 3, 5 .. of its range, merged through
+// LDS at the end; for one block (no blk2).
+// kSplit (kDual only): the work-group computes piece sp.piece of its query
 // block's key range (prefill_pieces), writing partials to sp when the block
 // has more than one piece and the normalised output otherwise.
-template <bool kTableInLds, int NW, bool kSplit = false>
+template <bool kTableInLds, int NW, bool kDual = false, bool kSplit = false>
 __device__ __forceinline__ void
 prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
-              const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
-              const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
-              const int32_t *__restrict__ bt, int bt_stride, int hkv, int group, int num_pages,
-              float scale_log2, int paired, int n_hgroups,
-              // work-group coordinates (x: query block and heads, b: sequence)
-              // and the LDS buffers: K and V tiles (2 * TILE each, 1024-byte
-              // aligned) and the block-table copy (kBtCache entries)
-              const int x, const int b, uint16_t *s_k, uint16_t *s_v, int32_t *s_bt, const SplitOut sp = {}) {
+              const uint16_t *__restrict__ q, uint16_t *__restrict__ out, const int32_t *__restrict__ bt,
+              int bt_stride, int hkv, int group, int num_pages, float scale_log2,
+              // the block(s) to run, and the LDS buffers: K and V tiles
+              // (2 * TILE each, or 4 * TILE with kDual, 1024-byte aligned) and
+              // the block-table copy (kBtCache entries)
+              const Item item, uint16_t *s_k, uint16_t *s_v, int32_t *s_bt, const SplitOut sp = {}) {
     static_assert(NW == 8 || NW == 4, "8 or 4 waves");
-    static_assert(!kSplit || NW == 4, "the key-range split runs 4-wave blocks");
-    constexpr int kBM = 8 * NW;         // query positions per block
+    static_assert(!kDual || NW == 8, "two groups of four waves");
+    static_assert(!kSplit || kDual, "the key-range split runs dual blocks");
+    constexpr int kBR = kDual ? 128 : 32 * NW;  // query rows per block
     constexpr int kNT = 64 * NW;        // threads
     constexpr int kRows = 64 / NW;      // tile rows (keys) each wave loads
     constexpr int kJ = kRows / 4;       // 1-KB loads per wave per K (or V) tile
     constexpr int kEvery = 8 / kJ;      // QK MFMAs between two of this wave's loads
-    // Work-group = one query block of one (sequence, kv head, head group),
-    // heaviest blocks first, or (paired) the pair of blocks nqb-1-i and i:
-    // causal blocks grow linearly with the block index, so every pair costs
-    // about the same number of key tiles.
-    const int kvh = x % hkv;
-    const int hg = (x / hkv) % n_hgroups;
-    const int pair = x / (hkv * n_hgroups);
-    const int row0 = qo_indptr[b];
-    const int n = qo_indptr[b + 1] - row0;
-    const int nqb = (n + kBM - 1) / kBM;
-    if (pair >= (paired ? (nqb + 1) / 2 : nqb)) return;
-    const int n_items = (!paired || pair == nqb - 1 - pair) ? 1 : 2;
-    const int r = prefix_lens[b];
+    const int b = item.b, kvh = item.kvh, row0 = item.row0, n = item.n, r = item.r;
+    const int rows = n * group;
+    // key tiles of block qb: those of its last row's position
+    auto block_tiles = [&](int qb) __attribute__((always_inline)) {
+        return (r + (min((qb + 1) * kBR, rows) + group - 1) / group + BN - 1) / BN;
+    };
+    const int nt_a = block_tiles(item.blk);  // the heavier block's
     // key tiles [t_lo, t_hi) of this work-group's (single) block and its
     // number of pieces (1 without the split); tile t_lo is loaded first and
     // page p of the sequence sits at s_bt[p - 4 t_lo] in the table copy
-    int t_lo = 0, t_hi = 0, n_pieces = 1;
+    int t_lo = 0, t_hi = nt_a, n_pieces = 1;
     if constexpr (kSplit) {
-        const int nt_b = prefill_block_tiles(r, n, nqb - 1 - pair);
-        n_pieces = prefill_pieces(nt_b, sp.piece_tiles, sp.max_pieces);
+        n_pieces = prefill_pieces(nt_a, sp.piece_tiles, sp.max_pieces);
         if (sp.piece >= n_pieces) return;
-        t_lo = sp.piece * nt_b / n_pieces;
-        t_hi = (sp.piece + 1) * nt_b / n_pieces;
+        t_lo = sp.piece * nt_a / n_pieces;
+        t_hi = (sp.piece + 1) * nt_a / n_pieces;
     }
     const int pbase = 4 * t_lo;
     const int32_t *btrow = bt + static_cast<size_t>(b) * bt_stride;
@@ -180,18 +274,23 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
-    const int hl = hg * 4 + (wave & 3);  // head within the kv group
-    const bool active = hl < group;
     const int hq = hkv * group;
-    const int h = kvh * group + (active ? hl : 0);
     const int l32 = lane & 31, g = lane >> 5;
+    // quotient of a row offset o < group + 32 by group: a product with the
+    // rounded-up reciprocal is exact while o * group < 2^16
+    // (groups of up to 32; for larger ones the quotient is 0 or 1)
+    const int recip = group <= 32 ? 65536 / group + 1 : 0;
+    const int one_at = group <= 32 ? 1 << 30 : group;
+    auto over_group = [&](int o) __attribute__((always_inline)) { return ((o * recip) >> 16) + (o >= one_at); };
 
-    // block-table entries of this work-group's keys (the heavier block's)
-    {
-        const int nt_a = (r + min((nqb - pair) * kBM, n) + BN - 1) / BN;
-        const int np_wg = min(4 * (kSplit ? t_hi : nt_a), np_seq);
-        for (int i = pbase + threadIdx.x; i < min(np_wg, pbase + kBtCache); i += kNT) s_bt[i - pbase] = btrow[i];
-    }
+    // Block-table entries of this work-group's keys (the heavier block's): two
+    // per thread are requested here, ahead of the first tile and Q, and stored
+    // to LDS behind them, so that the three latencies overlap (waiting for
+    // each in turn made a work-group's start 3.4 us of ~20).
+    const int np_wg = min(4 * t_hi, np_seq), bt_end = min(np_wg, pbase + kBtCache);
+    int32_t bt_first[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) bt_first[k] = btrow[min(pbase + static_cast<int>(threadIdx.x) + k * kNT, bt_end - 1)];
     const int seq_len = r + n;
 
     // ---- per-lane byte offsets, computed once
@@ -221,14 +320,31 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         goff[j] = 2 * (row * kHeadDim + 8 * ((lane & 15) ^ swz(row)));
     }
     const int lpage = kRows * wave / 16;  // page of the tile this wave loads
+    const int grp = NW == 8 ? wave >> 2 : 0;  // wave group of the 8-wave bodies
+    uint16_t *const sk = s_k + (kDual ? grp * 2 * TILE : 0);  // the tile buffers the wave reads
+    uint16_t *const sv = s_v + (kDual ? grp * 2 * TILE : 0);
+    // whole-page loads of the 8-wave bodies: 4 KB of K or V in four loads
+    const int lw = wave & 3;  // page of the tile
+    int goffp[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int row = 4 * j + (lane >> 4);
+        goffp[j] = 2 * (row * kHeadDim + 8 * ((lane & 15) ^ swz(row)));
+    }
 
     // per-item state
-    int qblk = 0, nt = 0, pos = 0, qabs = 0, diag = 0;
+    int nt = 0, qabs = 0, diag = 0;
+    int pos0 = 0, head0 = 0;   // position and head of the wave's first row
     uint4 qop[8];
     f32x16 oacc[4];
     f32x16 sacc[2];
     uint4 pop[4];
-    float m_run = -INFINITY;
+    // With kDual a row may see no key of a group's first tiles (they lie past
+    // its position): starting from the lowest finite value instead of -inf
+    // keeps its probabilities there at 2^(-inf) = 0 (and not at NaN), and any
+    // real score still raises it.
+    constexpr float kNoMax = kDual ? -__FLT_MAX__ : -INFINITY;
+    float m_run = kNoMax;
     float l_run = 0.f;
 
     // The (page, kv head) block of sequence page p (uniform per wave): its pool
@@ -278,6 +394,12 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             goff[j], 0, 0, 0);
     };
 
+    auto page_load_full = [&](__amdgpu_buffer_rsrc_t rsrc, uint16_t *dst, int j) __attribute__((always_inline)) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rsrc, reinterpret_cast<lds_void *>(reinterpret_cast<uintptr_t>(dst + (16 * lw + 4 * j) * ROW)), 16,
+            goffp[j], 0, 0, 0);
+    };
+
     // Matrix work: O^T += V^T P^T with V from tile buffer vbuf (if PV), then
     // S^T = K Q^T with K from tile buffer kbuf (if QK); `load(j)` is called
     // after every kEvery-th MFMA of a QK-only phase.  Operation i < npv is PV
@@ -286,8 +408,8 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         constexpr bool PV = decltype(pv_flag)::value, QK = decltype(qk_flag)::value;
         constexpr int npv = PV ? 16 : 0;
         constexpr int nop = npv + (QK ? 16 : 0);
-        const char *vb_ = reinterpret_cast<const char *>(s_v + vbuf * TILE);
-        const char *kb_ = reinterpret_cast<const char *>(s_k + kbuf * TILE);
+        const char *vb_ = reinterpret_cast<const char *>(sv + vbuf * TILE);
+        const char *kb_ = reinterpret_cast<const char *>(sk + kbuf * TILE);
         // per-read offsets are recomputed here (one XOR each) rather than held
         // in registers across the loop
         int ko = koff, vo0 = voff[0], vo1 = voff[1];
@@ -325,14 +447,17 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             }
             if (i + kAhead < nop) opnd[i % kAhead] = fetch(i + kAhead);
             if (!PV && i % kEvery == kEvery - 1) load(i / kEvery);
+            if (PV && kDual && i % 8 == 3) load(i / 8);
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
     };
 
     // Causal mask and online softmax of S(t) into P(t).
-    auto softmax_phase = [&](int t) __attribute__((always_inline)) {
+    auto softmax_phase = [&](int t, auto load) __attribute__((always_inline)) {
         const int k0 = t * BN;
+        load(0);
+        load(1);
         if (k0 + BN - 1 > diag) {
 #pragma unroll
             for (int blk = 0; blk < 2; ++blk)
@@ -361,6 +486,8 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
 #pragma unroll
                 for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
         }
+        load(2);
+        load(3);
         // key-step ks covers registers 8a..8a+7 of block ks/2, i.e. keys
         // 16ks + 8(e/4) + 4g + e%4 for operand element e
         float lsum[4];
@@ -373,6 +500,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             pop[kstep] = make_uint4(cvt2(p[0], p[1]), cvt2(p[2], p[3]), cvt2(p[4], p[5]), cvt2(p[6], p[7]));
             // row sums in fp32 with plain adds: a dot product over the bf16
             // values would wait behind the other wave's MFMAs on this SIMD
+            load(4 + kstep);
             lsum[kstep] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
         }
         l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
@@ -393,33 +521,128 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         }
     };
 
-    for (int item = 0; item < n_items; ++item) {
-        qblk = item == 0 ? nqb - 1 - pair : pair;
-        nt = (r + min(qblk * kBM + kBM, n) + BN - 1) / BN;
-        pos = qblk * kBM + (wave >> 2) * 32 + l32;  // this lane's query column
+    for (int pass = 0; pass < (item.blk2 >= 0 ? 2 : 1); ++pass) {
+        const int qblk = pass == 0 ? item.blk : item.blk2;
+        nt = block_tiles(qblk);
+        const int wrow = qblk * kBR + (kDual ? lw : wave) * 32;  // the wave's first row
+        pos0 = wrow / group;
+        head0 = wrow - pos0 * group;
+        const int o = head0 + l32, dpos = over_group(o);
+        const int pos = pos0 + dpos;        // this lane's query column
+        const int hrow = o - dpos * group;  // and its head in the group
         qabs = r + pos;
-        diag = r + qblk * kBM + (wave >> 2) * 32;  // smallest query of the wave
-        if (item > 0) wg_barrier();  // the previous item's output staging is done
-        first_tile(flag<NW == 4>());
-        // Q^T operand, all 8 dim-steps (k = 16*kb + 8*g + e)
-        {
-            const bool ok = active && pos < n;
-            const uint16_t *qp = q + (static_cast<size_t>(row0 + (ok ? pos : 0)) * hq + h) * kHeadDim + 8 * g;
+        diag = r + pos0;                    // smallest query of the wave
+        if (pass > 0) wg_barrier();  // the previous block's output staging is done
+        PageRef ref_0{0, 0}, ref_1{0, 0};  // kDual: page lw of the group's first two tiles
+        if constexpr (kDual) {
+            // pages straight from the block table in HBM (the LDS copy is not
+            // complete yet)
+            const int p0 = pbase + 4 * grp + lw, p1 = p0 + 8;
+            ref_0 = page_ref(p0, p0 < min(4 * t_hi, np_seq) ? btrow[p0] : -1);
+            ref_1 = page_ref(p1, p1 < min(4 * t_hi, np_seq) ? btrow[p1] : -1);
+            const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, ref_0);
 #pragma unroll
-            for (int kb = 0; kb < 8; ++kb)
-                qop[kb] = ok ? *reinterpret_cast<const uint4 *>(qp + 16 * kb) : make_uint4(0, 0, 0, 0);
+            for (int j = 0; j < 4; ++j) page_load_full(rk, sk, j);
+        } else {
+            first_tile(flag<NW == 4>());
+        }
+        // Q^T operand, all 8 dim-steps (k = 16*kb + 8*g + e).  Rows past the
+        // sequence's end take the last row's: their results are not stored
+        {
+            const uint16_t *qp =
+                q + (static_cast<size_t>(row0 + min(pos, n - 1)) * hq + kvh * group + hrow) * kHeadDim + 8 * g;
+#pragma unroll
+            for (int kb = 0; kb < 8; ++kb) qop[kb] = *reinterpret_cast<const uint4 *>(qp + 16 * kb);
         }
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-        m_run = -INFINITY;
+        m_run = kNoMax;
         l_run = 0.f;
-        if (item == 0) __syncthreads();  // s_bt
+        if (pass == 0) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int i = pbase + static_cast<int>(threadIdx.x) + k * kNT;
+                if (i < bt_end) s_bt[i - pbase] = bt_first[k];
+            }
+            for (int i = pbase + static_cast<int>(threadIdx.x) + 2 * kNT; i < bt_end; i += kNT)
+                s_bt[i - pbase] = btrow[i];
+            __syncthreads();
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        if constexpr (kDual) {  // V(0) and K(1), waited for at the end of M(0)
+            const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_0), rk = page_rsrc(kpool, ref_1);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                page_load_full(rv, sv, j);
+                page_load_full(rk, sk + TILE, j);
+            }
+        }
         wg_barrier();
 
-        if constexpr (NW == 8) {
+        if constexpr (kDual) {
+            // As the 8-wave body below, each group runs M(0) S(0) M(1) ..
+            // S(own-1) M(own) over its own tiles, with its own K and V buffers,
+            // group 1 one phase after group 0, so that one group's matrix phase
+            // runs beside the other's softmax.  A group loads its K(u+2) and
+            // V(u+1) at the start of its softmax S(u), into the buffers that
+            // M(u) was the last to read, and waits for them at the end of
+            // M(u+1): a period and a half before their first use in M(u+2).
+            const int total = t_hi - t_lo, periods = (total + 1) / 2;
+            const int own = grp == 0 ? periods : total / 2;  // tiles of this group
+            const auto tile = [&](int u) __attribute__((always_inline)) { return t_lo + 2 * u + grp; };
+            // page lw of the group's tile u, its entry read a period ahead
+            auto table_entry = [&](int u) __attribute__((always_inline)) {
+                const int p = 4 * tile(u) + lw;
+                const bool ok = u < own && p < np_seq;
+                if constexpr (kTableInLds)
+                    return s_bt[ok ? p - pbase : 0];
+                else
+                    return ok ? (p - pbase < kBtCache ? s_bt[p - pbase] : btrow[p]) : -1;
+            };
+            int pg_n = kTableInLds ? table_entry(2) : 0;
+            PageRef ref_v = ref_1;  // page lw of tile u + 1, whose V is loaded in S(u)
+            auto period_loads = [&](int u) __attribute__((always_inline)) {
+                PageRef ref_k;
+                if constexpr (kTableInLds) {
+                    ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(pg_n));
+                    pg_n = table_entry(u + 3);
+                } else {
+                    ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(table_entry(u + 2)));
+                }
+                // (no bytes past the group's last tile: the loads return zeros)
+                const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, u + 2 < own ? ref_k : PageRef{0, 0});
+                const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_v);
+                softmax_phase(tile(u), [&](int j) __attribute__((always_inline)) {
+                    if (j >= 4) page_load_full(rk, sk + (u & 1) * TILE, j - 4);
+                });
+                __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4): all but the K loads just issued
+                wg_barrier();
+                mfma_phase(flag<true>(), flag<true>(), (u + 1) & 1, u & 1, [&](int j) __attribute__((always_inline)) {
+                    page_load_full(rv, sv + ((u + 1) & 1) * TILE, j);
+                });
+                wg_barrier();
+                ref_v = ref_k;
+            };
+            auto vm_wait = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
+            if (grp == 1) wg_barrier();
+            if (own > 0) {
+                mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});
+                vm_wait();
+                wg_barrier();
+                for (int u = 0; u + 1 < own; ++u) {
+                    period_loads(u);
+                }
+                softmax_phase(tile(own - 1), [](int) {});
+                vm_wait();
+                wg_barrier();
+                mfma_phase(flag<true>(), flag<false>(), 0, (own - 1) & 1, [](int) {});
+                wg_barrier();
+            }
+            // 2 periods + 2 barriers in all for both groups
+            for (int i = own > 0 ? 2 * own + 1 : 0; i < 2 * periods + (grp == 0 ? 2 : 1); ++i) wg_barrier();
+        } else if constexpr (NW == 8) {
             // Two groups of four waves (one wave of each on every SIMD), half a
             // period apart: while one group runs its matrix phase M(t) =
             // O += V(t-1)^T P(t-1)^T, S(t) = K(t) Q^T, the other runs the
@@ -432,7 +655,6 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             // loaded during period t (into the buffers K(t-1) and V(t-2) used)
             // and waited for at its end.  Row sums are plain fp32 adds: a dot
             // product instruction would wait behind the other group's MFMAs.
-            const int grp = wave >> 2;
             // Each wave runs its own sequence M(0) S(0) M(1) .. S(nt-1) M(nt),
             // group 1 one phase after group 0 (a barrier ends every phase, 2nt+2
             // in all for both groups).  Group 1 issues all loads of period t
@@ -440,18 +662,6 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             // phase 2t, its softmax phase, and waits for them at the end of
             // phase 2t+1: group 0's matrix phases issue only MFMAs and their
             // operand reads.
-            const int lw = wave & 3;  // page of the tile a group-1 wave loads
-            int goffp[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int row = 4 * j + (lane >> 4);
-                goffp[j] = 2 * (row * kHeadDim + 8 * ((lane & 15) ^ swz(row)));
-            }
-            auto page_load_full = [&](__amdgpu_buffer_rsrc_t rsrc, uint16_t *dst, int j) __attribute__((always_inline)) {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rsrc, reinterpret_cast<lds_void *>(reinterpret_cast<uintptr_t>(dst + (16 * lw + 4 * j) * ROW)),
-                    16, goffp[j], 0, 0, 0);
-            };
             // Block-table entry of page lw of tile it.  With the whole table in
             // LDS it is read one period before its loads (pg_n), so they never
             // wait for an LDS read, and taken as read (entry 0 past the
@@ -494,34 +704,33 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 period_loads(0);
                 wg_barrier();
             }
-            if (active) mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});  // M(0): S(0) = K(0) Q^T
+            mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});  // M(0): S(0) = K(0) Q^T
             if (grp == 1) vm_wait();
             wg_barrier();
             for (int t = 0; t + 1 < nt; ++t) {
                 if (grp == 1) period_loads(t + 1);
-                if (active) softmax_phase(t);
+                softmax_phase(t, [](int) {});
                 wg_barrier();
-                if (active)  // M(t+1): O += V(t)^T P(t)^T, S(t+1) = K(t+1) Q^T
-                    mfma_phase(flag<true>(), flag<true>(), (t + 1) & 1, t & 1, [](int) {});
+                // M(t+1): O += V(t)^T P(t)^T, S(t+1) = K(t+1) Q^T
+                mfma_phase(flag<true>(), flag<true>(), (t + 1) & 1, t & 1, [](int) {});
                 if (grp == 1) vm_wait();
                 wg_barrier();
             }
             // the last tile: softmax(nt-1), then M(nt) = O += V(nt-1)^T P(nt-1)^T
-            if (active) softmax_phase(nt - 1);
+            softmax_phase(nt - 1, [](int) {});
             wg_barrier();
-            if (active) mfma_phase(flag<true>(), flag<false>(), 0, (nt - 1) & 1, [](int) {});
+            mfma_phase(flag<true>(), flag<false>(), 0, (nt - 1) & 1, [](int) {});
             wg_barrier();
             if (grp == 0) wg_barrier();  // group 0's last phase: none of its own work
         } else
         // Tile t+1 is loaded (into the other buffer) while tile t is processed;
         // the K and V pages of a tile are the same pages of the pool.
-        for (int t = t_lo; t < (kSplit ? t_hi : nt); ++t) {
-            const int u = t - t_lo;  // tile buffer parity
-            const bool more = t + 1 < (kSplit ? t_hi : nt);
+        for (int t = 0; t < nt; ++t) {
+            const bool more = t + 1 < nt;
             const PageRef ref = more ? tile_page(t + 1) : PageRef{0, 0};
             const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, ref), rv = page_rsrc(vpool, ref);
-            uint16_t *dk = s_k + ((u + 1) & 1) * TILE;
-            uint16_t *dv = s_v + ((u + 1) & 1) * TILE;
+            uint16_t *dk = s_k + ((t + 1) & 1) * TILE;
+            uint16_t *dv = s_v + ((t + 1) & 1) * TILE;
             auto load = [&](int j) __attribute__((always_inline)) {
                 if (more) {
                     if (j < kJ)
@@ -530,50 +739,105 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                         page_load(rv, dv, j - kJ);
                 }
             };
-            if (active) {
-                mfma_phase(flag<false>(), flag<true>(), u & 1, u & 1, load);
-                softmax_phase(t);
-                mfma_phase(flag<true>(), flag<false>(), u & 1, u & 1, [](int) {});
-            } else {
-#pragma unroll
-                for (int j = 0; j < 2 * kJ; ++j) load(j);
-            }
+            mfma_phase(flag<false>(), flag<true>(), t & 1, t & 1, load);
+            softmax_phase(t, [](int) {});
+            mfma_phase(flag<true>(), flag<false>(), t & 1, t & 1, [](int) {});
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's direct loads landed
             wg_barrier();
         }
 
-        if constexpr (kSplit) {
-            if (n_pieces > 1) {
-                // ---- this piece's partial: (m, l) and the unnormalised O of
-                // every row, fp32.  The wave's 32 x 128 tile (16 KiB; waves 0-1
-                // in the K buffers, 2-3 in the V buffers) is staged in LDS so
-                // every store writes whole 512-byte rows; row q holds its
-                // 16-byte chunk c (dims 4c..4c+3) at chunk c ^ (q % 32).
-                const float lt = l_run + __shfl_xor(l_run, 32);
-                char *st = reinterpret_cast<char *>(wave < 2 ? s_k : s_v) + (wave & 1) * (32 * 512);
+        if constexpr (kDual) {
+            // ---- merge the groups: waves w and w + 4 hold the same rows over
+            // different keys.  Group 0 finishes dims 0..63 and group 1 dims
+            // 64..127: each hands the other half of its O (8 KiB per wave, in
+            // its own K buffers, as float4 per lane) with its (m, l).
+            const float lt = l_run + __shfl_xor(l_run, 32);
+            f32x16 keep[2];
+            {
+                float4 *give = reinterpret_cast<float4 *>(sk) + lw * 512;
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < 2; ++db) {
+                    const f32x16 gv = grp == 0 ? oacc[2 + db] : oacc[db];
+                    keep[db] = grp == 0 ? oacc[db] : oacc[2 + db];
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4)
+                        give[(4 * db + i4) * 64 + lane] =
+                            make_float4(gv[4 * i4], gv[4 * i4 + 1], gv[4 * i4 + 2], gv[4 * i4 + 3]);
+                }
+                if (g == 0) reinterpret_cast<float2 *>(sv)[lw * 32 + l32] = make_float2(m_run, lt);
+            }
+            __syncthreads();
+            float inv, m_all, l_all;
+            {
+                const uint16_t *pk = s_k + (1 - grp) * 2 * TILE, *pv = s_v + (1 - grp) * 2 * TILE;
+                const float2 ml = reinterpret_cast<const float2 *>(pv)[lw * 32 + l32];
+                m_all = vmax(m_run, ml.x);
+                const float wa = __builtin_amdgcn_exp2f(m_run - m_all), wb = __builtin_amdgcn_exp2f(ml.x - m_all);
+                l_all = wa * lt + wb * ml.y;
+                inv = 1.f / l_all;
+                const float4 *got = reinterpret_cast<const float4 *>(pk) + lw * 512;
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const float4 v = got[(4 * db + i4) * 64 + lane];
+                        keep[db][4 * i4 + 0] = wa * keep[db][4 * i4 + 0] + wb * v.x;
+                        keep[db][4 * i4 + 1] = wa * keep[db][4 * i4 + 1] + wb * v.y;
+                        keep[db][4 * i4 + 2] = wa * keep[db][4 * i4 + 2] + wb * v.z;
+                        keep[db][4 * i4 + 3] = wa * keep[db][4 * i4 + 3] + wb * v.w;
+                    }
+            }
+            // the wave's 32 x 64 half tile, staged in the rest of its V buffers
+            // (past the (m, l) words) so that stores write whole half rows
+            char *st = reinterpret_cast<char *>(sv) + 1024 + lw * (32 * 256);
+            if (kSplit && n_pieces > 1) {
+                // this piece's partial: (m, l) and the unnormalised O, fp32;
+                // row q holds its 16-byte chunk c at chunk c ^ (q % 16)
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
 #pragma unroll
                     for (int i4 = 0; i4 < 4; ++i4) {
                         const int c = 8 * db + 2 * i4 + g;
-                        *reinterpret_cast<float4 *>(st + l32 * 512 + 16 * (c ^ l32)) =
-                            make_float4(oacc[db][4 * i4 + 0], oacc[db][4 * i4 + 1], oacc[db][4 * i4 + 2],
-                                        oacc[db][4 * i4 + 3]);
+                        *reinterpret_cast<float4 *>(st + l32 * 256 + 16 * (c ^ (l32 & 15))) =
+                            make_float4(keep[db][4 * i4], keep[db][4 * i4 + 1], keep[db][4 * i4 + 2],
+                                        keep[db][4 * i4 + 3]);
                     }
-                if (active) {
-                    const size_t slot = static_cast<size_t>(sp.piece) * sp.rows + row0;
+                const size_t slot = static_cast<size_t>(sp.piece) * sp.rows + row0;
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        const int row = 2 * j + (lane >> 5), c = lane & 31;
-                        const float4 v = *reinterpret_cast<const float4 *>(st + row * 512 + 16 * (c ^ row));
-                        const int prow = qblk * kBM + row;
-                        if (prow < n)
-                            *reinterpret_cast<float4 *>(sp.o + ((slot + prow) * hq + h) * kHeadDim + 4 * c) = v;
-                    }
-                    if (g == 0 && pos < n) sp.ml[(slot + pos) * hq + h] = make_float2(m_run, lt);
+                for (int j = 0; j < 8; ++j) {
+                    const int row = 4 * j + (lane >> 4), c = lane & 15;
+                    const float4 v = *reinterpret_cast<const float4 *>(st + row * 256 + 16 * (c ^ (row & 15)));
+                    const int oo = head0 + row, dp = over_group(oo);
+                    const int h = kvh * group + oo - dp * group;
+                    if (pos0 + dp < n)
+                        *reinterpret_cast<float4 *>(sp.o + ((slot + pos0 + dp) * hq + h) * kHeadDim + 64 * grp +
+                                                    4 * c) = v;
                 }
-                continue;
+                if (grp == 0 && g == 0 && pos < n)
+                    sp.ml[(slot + pos) * hq + kvh * group + hrow] = make_float2(m_all, l_all);
+            } else {
+                // normalised bf16; row q holds its 16-byte chunk c at c ^ (q % 8)
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const int c = 4 * db + i4;
+                        *reinterpret_cast<uint2 *>(st + l32 * 128 + 16 * (c ^ (l32 & 7)) + 8 * g) =
+                            make_uint2(cvt2(keep[db][4 * i4 + 0] * inv, keep[db][4 * i4 + 1] * inv),
+                                       cvt2(keep[db][4 * i4 + 2] * inv, keep[db][4 * i4 + 3] * inv));
+                    }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int row = 8 * j + (lane >> 3), c = lane & 7;
+                    const uint4 v = *reinterpret_cast<const uint4 *>(st + row * 128 + 16 * (c ^ (row & 7)));
+                    const int oo = head0 + row, dp = over_group(oo);
+                    const int h = kvh * group + oo - dp * group;
+                    if (pos0 + dp < n)
+                        *reinterpret_cast<uint4 *>(out + (static_cast<size_t>(row0 + pos0 + dp) * hq + h) * kHeadDim +
+                                                   64 * grp + 8 * c) = v;
+                }
             }
+            return;
         }
         // ---- normalise and write O[pos][h][d].  The wave's 32 x 128 tile is
         // staged in LDS (the K/V buffers are free now) so that every store
@@ -592,15 +856,15 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                     make_uint2(cvt2(oacc[db][4 * i4 + 0] * inv, oacc[db][4 * i4 + 1] * inv),
                                cvt2(oacc[db][4 * i4 + 2] * inv, oacc[db][4 * i4 + 3] * inv));
             }
-        if (active) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int row = 4 * j + (lane >> 4), c = lane & 15;
-                const uint4 v = *reinterpret_cast<const uint4 *>(st + row * 256 + 16 * (c ^ (row & 15)));
-                const int prow = qblk * kBM + (wave >> 2) * 32 + row;
-                if (prow < n)
-                    *reinterpret_cast<uint4 *>(out + (static_cast<size_t>(row0 + prow) * hq + h) * kHeadDim + 8 * c) = v;
-            }
+        for (int j = 0; j < 8; ++j) {
+            const int row = 4 * j + (lane >> 4), c = lane & 15;
+            const uint4 v = *reinterpret_cast<const uint4 *>(st + row * 256 + 16 * (c ^ (row & 15)));
+            const int oo = head0 + row, dp = over_group(oo);
+            const int h = kvh * group + oo - dp * group;
+            if (pos0 + dp < n)
+                *reinterpret_cast<uint4 *>(out + (static_cast<size_t>(row0 + pos0 + dp) * hq + h) * kHeadDim +
+                                           8 * c) = v;
         }
     }
 }

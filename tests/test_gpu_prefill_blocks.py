@@ -1,0 +1,97 @@
+"""Prefill query blocks on the GPU against the CPU oracle: rows of every GQA
+grouping laid end to end (block edges at 128 and 256 rows), the blocks whose
+keys two wave groups share, their key-range pieces, and the order of the blocks
+over a whole batch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2504_14489_amd import mw
+from paper_2504_14489_amd.device import Partition, to_bits
+from tests.helpers import assert_close, say
+from tests.test_gpu_prefill import _varlen_setup
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(hq, hkv, seqs, cus, seed):
+    """The batch through the split-enabled and the plain entry point on the
+    prefill stream of `cus` CUs (0: the whole GPU); every row of both against
+    the oracle."""
+    wls, k, v, bt, stride, q = _varlen_setup(seqs, hq, hkv, seed)
+    dev = torch.device("cuda:0")
+    t16 = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).to(dev)
+    t32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(dev)
+    dk, dv, dq, dbt = t16(k), t16(v), t16(q), t32(bt)
+    ns, rs = [n for _, n in seqs], [r for r, _ in seqs]
+    indptr, pref = t32(np.cumsum([0] + ns)), t32(rs)
+    pool = mw.mw_kv_pool_create(k.shape[0], 16, hkv, 128, dk.data_ptr(), dv.data_ptr())
+    part = Partition(cus, 256 - cus) if cus else None
+    outs = []
+    try:
+        stream = part.prefill_stream if part else 0
+        nbytes = mw.mw_prefill_workspace_size(hq, hkv, 128, ns, rs, 0)
+        ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev)
+        for split in (True, False):
+            do = torch.zeros_like(dq)
+            args = (pool, hq, hkv, 128, 1 / np.sqrt(128), ns, rs, indptr.data_ptr(), pref.data_ptr(), dbt.data_ptr(),
+                    stride, dq.data_ptr(), do.data_ptr())
+            if split:
+                mw.mw_prefill_attn_ws(*args, ws.data_ptr(), ws.numel(), stream)
+            else:
+                mw.mw_prefill_attn(*args, stream)
+            torch.cuda.synchronize()
+            outs.append(to_bits(do))
+    finally:
+        if part:
+            part.close()
+        mw.mw_kv_pool_destroy(pool)
+    for got, what in zip(outs, ("split-enabled", "plain")):
+        row = 0
+        for w, (r, n) in zip(wls, seqs):
+            if n:
+                ref = oracle.prefill(w.q_pre[r:r + n], w.k_pool, w.v_pool, w.pre_bt, r)
+                assert_close(got[row:row + n], ref, f"{what} hq={hq} hkv={hkv} r={r} n={n} cus={cus}")
+            row += n
+
+
+# one sequence, groups 1 .. 40 (above 32 a row offset holds one head change at
+# most): the last block full, one row short of it and one row over it; prefixes
+# that leave the diagonal inside one tile, across two and across three; on the
+# whole GPU and on 8 CUs (256-row blocks for the larger calls)
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (3, 1), (10, 2), (7, 1), (24, 2), (16, 1), (40, 1)])
+@pytest.mark.parametrize("cus", [0, 8])
+def test_prefill_row_blocks(hq, hkv, cus):
+    g = hq // hkv
+    for r, rows in ((0, 128), (63, 127), (64, 129), (130, 257), (1, 640)):
+        n = max(1, rows // g)
+        for nn in sorted({n, n + 1}):
+            say(f"prefill row blocks hq={hq} hkv={hkv} r={r} n={nn} cus={cus}")
+            _run(hq, hkv, [(r, nn)], cus, 500 + 7 * hq + nn)
+
+
+# (prefix, new): one to five key tiles (an odd count leaves a wave group without
+# its last tile, one tile leaves it without any; rows that see none of a
+# group's keys), and ranges long enough to be cut into several pieces
+@pytest.mark.parametrize("r,n", [(0, 1), (0, 64), (0, 65), (0, 128), (63, 66), (0, 200), (190, 127), (1500, 1),
+                                 (3000, 257), (9000, 40)])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (1, 1)])
+def test_prefill_shared_keys(r, n, hq, hkv):
+    say(f"prefill shared keys r={r} n={n} hq={hq} hkv={hkv}")
+    _run(hq, hkv, [(r, n)], 0, 900 + n)
+
+
+# batches at the limit of the ordering over the whole batch (64 sequences) and
+# past it, with empty sequences, equal ones and one much longer than the rest
+@pytest.mark.parametrize("batch", [2, 64, 65])
+@pytest.mark.parametrize("cus", [0, 8])
+def test_prefill_batch_order(batch, cus):
+    rng = np.random.default_rng(batch)
+    seqs = [(int(rng.integers(0, 90)), int(rng.integers(1, 40))) for _ in range(batch)]
+    seqs[0] = (300, 700)
+    if batch > 2:
+        seqs[3], seqs[batch - 1] = (5, 0), (17, 0)
+        seqs[10:20] = [(40, 33)] * 10
+    say(f"prefill batch order {batch} sequences on {cus or 'all'} CUs")
+    _run(8, 2, seqs, cus, 77)
