@@ -263,7 +263,9 @@ mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape *shape, in
  * "tab:theory_cost" fixes every row's key set, so the merged result is the same
  * attention).  Without pieces (a grid that fills the CUs, or blocks of at most
  * 4 key tiles) this is one launch, workspace unused.  With them, two launches
- * (split, merge), recorded as two kernels in `timing`.
+ * (split, merge), recorded as two kernels in `timing`.  A grid that does fill the
+ * CUs but would leave most of them idle in its last round runs that round as the
+ * smaller blocks (one launch, no workspace).
  * The split depends on the lengths and on the stream's CU count, never on
  * page ids; rounding may differ from mw_prefill_attn in the last bits.
  *

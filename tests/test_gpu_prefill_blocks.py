@@ -95,3 +95,15 @@ def test_prefill_batch_order(batch, cus):
         seqs[10:20] = [(40, 33)] * 10
     say(f"prefill batch order {batch} sequences on {cus or 'all'} CUs")
     _run(8, 2, seqs, cus, 77)
+
+
+# more than two rounds of 256-row blocks on 8 CUs, the last of at most half a
+# round (run as dual halves): one sequence of 17 and of 20 blocks (the heaviest
+# block one row long or full, so that a half may be empty), a batch whose
+# lightest block is long enough, groups of 4, 3 and 1
+@pytest.mark.parametrize("hq,hkv,seqs", [(4, 1, [(1500, 64 * 16 + 1)]), (4, 1, [(1500, 64 * 20)]),
+                                         (6, 2, [(1203, 85 * 8 + 7)]), (2, 2, [(3000, 9 * 256 + 130)]),
+                                         (4, 1, [(1400, 500), (1501, 513), (1333, 100)])])
+def test_prefill_last_round_in_halves(hq, hkv, seqs):
+    say(f"prefill last round in halves hq={hq} hkv={hkv} {seqs}")
+    _run(hq, hkv, seqs, 8, 1300)
