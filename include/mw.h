@@ -289,16 +289,15 @@ mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_shape *shape,
  * flash-decoding split of Sec. 2.2's memory-bound decode).  chunk_pages
  * chooses the split:
  *   0  (default) balanced: the segments laid end to end are cut into equal
- *      ranges of pages, two per CU of the stream the call runs on (at most
- *      512, at least 16 pages each); a range may cross segment boundaries and
- *      every CU streams the same number of bytes (when every sequence is
- *      long enough for two ranges or more, segments are padded to a multiple
- *      of the range instead, so that ranges do not straddle segments, if that
- *      keeps 90% of the work-groups).  The split depends on the lengths and
- *      on the stream's CU count.  One kernel: the work-group
- *      that finds every piece of a segment done (per-piece flags in the
- *      workspace, tagged per call, so the workspace needs no initialisation)
- *      merges that segment.
+ *      ranges of pages, one per CU of the stream the call runs on (at most
+ *      256, at least 16 pages each); a range may cross segment boundaries and
+ *      every CU streams the same number of bytes.  Where little is lost by it,
+ *      segments are padded to a multiple of the range instead, so that ranges
+ *      do not straddle segments, or each segment is a range of its own.  The
+ *      split depends on the lengths and on the stream's CU count.  One kernel:
+ *      the work-group that finds every piece of a segment done (per-piece
+ *      flags in the workspace, tagged per call, so the workspace needs no
+ *      initialisation) merges that segment.
  *   -1 fixed chunks chosen from the lengths: the largest of 128, 64 and 32
  *      pages that still gives at least 1024 (chunk, kv head) work units.
  *   8..256, a multiple of 8: fixed chunks of that many pages; a second

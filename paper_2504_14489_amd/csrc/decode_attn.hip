@@ -30,18 +30,16 @@ k_decode_split(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ 
 
 // Balanced split: unit u streams pages [u per_unit, (u + 1) per_unit) of the
 // batch's (sequence, kv head) segments laid end to end.
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kSpanThreads, 1)
 k_decode_balanced(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
                   const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
                   const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ bt, int bt_stride,
                   float *__restrict__ ws_o, float2 *__restrict__ ws_ml, uint32_t *__restrict__ flags,
                   uint32_t tag, int64_t slots, int batch, int hkv, int group, int num_pages, float scale_log2,
-                  int64_t per_unit, int64_t total, int aligned) {
-    __shared__ __attribute__((aligned(16))) uint16_t s_v[kWaves * kWaveBufElems];
-    __shared__ float s_m[kWaves][16];
-    __shared__ float s_l[kWaves][16];
+                  int per_unit, int total, int aligned) {
+    __shared__ __attribute__((aligned(16))) SpanLds lds;
     decode_span(kpool, vpool, q, out, seq_lens, bt, bt_stride, ws_o, ws_ml, flags, tag, slots, batch, hkv, group,
-                num_pages, scale_log2, per_unit, total, aligned != 0, blockIdx.x, threadIdx.x, s_v, s_m, s_l);
+                num_pages, scale_log2, per_unit, total, aligned != 0, blockIdx.x, threadIdx.x, lds);
 }
 
 // Combine of the fixed-chunk split: one work-group per (sequence, kv head);
@@ -62,14 +60,15 @@ k_decode_combine(uint16_t *__restrict__ out, const int32_t *__restrict__ seq_len
     merge_pieces(out, ws_o, ws_ml, first, hkv, nch, b, hkv, kvh, group, threadIdx.x);
 }
 
-// Balanced split: units per CU of the stream (two 4-wave work-groups fit a
-// CU), the most units (two per CU of a 256-CU device; the workspace is sized
-// for it) and the fewest pages a unit streams (two pairs per wave: short
-// calls are bound by latency, not bytes, and fewer, longer pieces leave less
-// to merge at the end).
-constexpr int64_t kBalancedPerCu = 2;
-constexpr int64_t kBalancedMaxUnits = 512;
+// Balanced split: units per CU of the stream (an 8-wave work-group fills a
+// CU), and the fewest pages a unit streams (a pair per wave: short calls are
+// bound by latency, not bytes, and fewer, longer pieces leave less to merge at
+// the end).  The workspace is sized for two units per CU of a 256-CU device.
+constexpr int64_t kBalancedPerCu = 1;
+constexpr int64_t kBalancedSizedUnits = 512;
+constexpr int64_t kBalancedMaxUnits = 256;
 constexpr int64_t kBalancedMinPages = 16;
+constexpr int64_t kBalancedMergeSteps = 3;  // a merge's time in steps of a wave
 
 struct Plan {
     int64_t units;            // work-groups of the split kernel
@@ -141,57 +140,77 @@ mw_status plan_decode(const mw_attn_shape *shape, int32_t batch, const int32_t *
     // the CUs
     auto balanced = [&](int64_t n_cus, Plan *pl, bool may_align) {
         pl->chunk_pages = 0;
-        pl->total = count(1) * hkv;
-        int64_t units = std::min(kBalancedPerCu * std::max<int64_t>(n_cus, 1), kBalancedMaxUnits);
-        units = std::max<int64_t>(1, std::min(units, (pl->total + kBalancedMinPages - 1) / kBalancedMinPages));
-        pl->per_unit = std::max<int64_t>(1, (pl->total + units - 1) / units);
-        // Few long segments (each cut into two pieces or more): pad every
-        // segment to a multiple of the range, so that a unit holds one piece
-        // of one segment (a range that straddles two segments costs a second
-        // piece set-up and a second merge at the end).  The range is the
-        // shortest one, no shorter than the balanced one, whose padded
-        // segments need no more units than the balanced split (equal segments
-        // are then cut in equal pieces); padding is used only if it keeps at
-        // least 90% of those units busy.
         pl->aligned = false;
-        int64_t np_min = INT64_MAX, np_max = 0;
-        for (int32_t b = 0; b < batch; ++b) {
-            const int64_t np = (h_seq_lens[b] + kPageSize - 1) / kPageSize;
-            np_min = std::min(np_min, np);
-            np_max = std::max(np_max, np);
-        }
-        const int64_t units_bal = (pl->total + pl->per_unit - 1) / pl->per_unit;
+        const int64_t pages = count(1) * hkv, segs = static_cast<int64_t>(batch) * hkv;
+        // the workspace holds two units per CU's pieces
+        const auto ranges = [&](int64_t most) {
+            const int64_t n = std::max<int64_t>(1, std::min(most, (pages + kBalancedMinPages - 1) / kBalancedMinPages));
+            return std::max<int64_t>(1, (pages + n - 1) / n);
+        };
+        const int64_t sized_range = ranges(std::min(2 * std::max<int64_t>(n_cus, 1), kBalancedSizedUnits));
+        const int64_t sized = (pages + sized_range - 1) / sized_range;
+        const int64_t most = std::min(kBalancedPerCu * std::max<int64_t>(n_cus, 1), kBalancedMaxUnits);
+        pl->per_unit = ranges(most);
+        pl->total = pages;
+        int64_t np_max = 0;
+        for (int32_t b = 0; b < batch; ++b)
+            np_max = std::max<int64_t>(np_max, (h_seq_lens[b] + kPageSize - 1) / kPageSize);
+        const int64_t units_bal = (pages + pl->per_unit - 1) / pl->per_unit;
         auto padded_units = [&](int64_t r) {
             int64_t n = 0;
             for (int32_t b = 0; b < batch; ++b) n += ((h_seq_lens[b] + kPageSize - 1) / kPageSize + r - 1) / r;
             return n * hkv;
         };
-        if (may_align && batch > 0 && np_min >= 2 * pl->per_unit) {
-            int64_t lo = pl->per_unit, hi = np_max;  // padded_units(np_max) = batch * hkv <= units_bal / 2
-            while (lo < hi) {
-                const int64_t mid = lo + (hi - lo) / 2;
-                if (padded_units(mid) <= units_bal)
-                    hi = mid;
-                else
-                    lo = mid + 1;
-            }
-            const int64_t n = padded_units(lo);
-            if (10 * n >= 9 * units_bal) {
-                pl->aligned = true;
-                pl->per_unit = lo;
-                pl->total = n * lo;
+        auto align_to = [&](int64_t r) {
+            pl->aligned = true;
+            pl->per_unit = r;
+            pl->total = padded_units(r) * r;
+        };
+        // a wave's pairs in a range of r pages
+        auto steps = [](int64_t r) { return ((r + 7) / 8 + 1) / 2; };
+        if (may_align && batch > 0 && segs <= most) {
+            if (steps(np_max) <= steps(pl->per_unit) + kBalancedMergeSteps) {
+                // Every segment whole in a unit of its own, if its few more
+                // steps (1.3 us each) cost no more than storing, flagging and
+                // merging its pieces (about 4 us).
+                align_to(std::max(kBalancedMinPages, np_max));
+            } else {
+                // Pad every segment to a multiple of the range, so that a unit
+                // holds one piece of one segment (a range that straddles two
+                // leaves two pieces to merge).  The range is the shortest one,
+                // no shorter than the balanced one, whose padded segments need
+                // no more units than CUs (equal segments are then cut in equal
+                // pieces).  Padding is used only if it leaves at least 70% of
+                // the balanced split's units and 70% of their pages, and
+                // idles no more than 20000 pages (164 MB): over 30 batches of
+                // 1 to 128 sequences of 64 to 32000 tokens it then takes up to
+                // 16% less (128 skewed sequences of one kv head 29.7 -> 24.9
+                // us) and never more, and past these lines up to 5% more (30 of
+                // 16000 to 32000 tokens, 137000 idle pages, 454 -> 476 us).
+                int64_t lo = pl->per_unit, hi = std::max(np_max, lo);
+                while (lo < hi) {
+                    const int64_t mid = lo + (hi - lo) / 2;
+                    if (padded_units(mid) <= most)
+                        hi = mid;
+                    else
+                        lo = mid + 1;
+                }
+                const int64_t n = padded_units(lo);
+                if (n <= sized + segs - 1 && 10 * n >= 7 * units_bal && 10 * pages >= 7 * n * lo &&
+                    n * lo - pages <= 20000)
+                    align_to(lo);
             }
         }
         pl->units = pl->total > 0 ? (pl->total + pl->per_unit - 1) / pl->per_unit : 0;
-        // piece of unit u of segment s in slot u + s
-        pl->slots = pl->units > 0 ? pl->units + static_cast<int64_t>(batch) * hkv - 1 : 0;
+        // piece of unit u of segment s in slot u + s, or in slot u when aligned
+        pl->slots = pl->units > 0 ? sized + segs - 1 : 0;
         plan_layout(pl, batch, group);
     };
     if (chunk_pages == 0 && cus < 0) {
         // workspace for either split of chunk_pages = 0
         Plan a, b;
         fixed(0, &a);
-        balanced(kBalancedMaxUnits, &b, false);
+        balanced(kBalancedSizedUnits, &b, false);
         *plan = a.bytes >= b.bytes ? a : b;
     } else if (chunk_pages == 0 && cus > 0) {
         balanced(cus, plan, true);
@@ -291,13 +310,13 @@ mw_status decode_launch(const mw_decode_args &a, const DecodePlan &pl, hipStream
     if (pl.units > 0) {
         char *ws = static_cast<char *>(a.d_workspace);
         if (pl.per_unit > 0) {
-            hipLaunchKernelGGL(k_decode_balanced, dim3(static_cast<unsigned>(pl.units)), dim3(kThreads), 0, s,
+            hipLaunchKernelGGL(k_decode_balanced, dim3(static_cast<unsigned>(pl.units)), dim3(kSpanThreads), 0, s,
                                pool->k, pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out),
                                d_seq_lens, d_block_table, bt_stride, reinterpret_cast<float *>(ws),
                                reinterpret_cast<float2 *>(ws + pl.off_ml),
                                reinterpret_cast<uint32_t *>(ws + pl.off_meta), next_tag(), pl.slots,
-                               batch, pl.hkv, pl.group, pool->desc.num_pages, pl.scale_log2, pl.per_unit, pl.total,
-                               pl.aligned ? 1 : 0);
+                               batch, pl.hkv, pl.group, pool->desc.num_pages, pl.scale_log2,
+                               static_cast<int>(pl.per_unit), static_cast<int>(pl.total), pl.aligned ? 1 : 0);
             st = check_launch("k_decode_balanced");
         } else {
             hipLaunchKernelGGL(k_decode_split, dim3(static_cast<unsigned>(pl.units)), dim3(kThreads), 0, s,
