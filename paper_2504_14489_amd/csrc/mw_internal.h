@@ -133,8 +133,10 @@ struct PrefillPlan {
     int pieces;           // most pieces of any block; 1: no split
     int piece_tiles;      // target key tiles per piece
     int64_t rows;         // sum of the new lengths (rows of the workspace partials)
+    int body;             // a 4-wave plan's body where key ranges may be split
     size_t split_bytes;   // workspace the split needs
 };
+enum { kBodyPlain = 0, kBodyDual = 1, kBodyEight = 2 };  // as planned; dual blocks; 8-wave single blocks
 // Validates a prefill call's arguments and plans it for a stream that may use
 // `cus` CUs (block pairing and, with allow_small, the work-group size depend
 // on it).
@@ -144,9 +146,9 @@ mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_smal
 // prefill_prepare and by the latency predictor, which simulates the launch.
 void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int group, int64_t cus,
                           bool allow_small, PrefillPlan *p);
-// Plans the key-range split of a 4-wave call on `cus` CUs (cus = 0: the
-// largest split any stream could take); fills pieces, piece_tiles, rows and
-// split_bytes.  Lengths must have been validated.
+// Plans the body and the key-range split of a 4-wave call on `cus` CUs (cus = 0:
+// the largest split any stream could take); fills body, pieces, piece_tiles,
+// rows and split_bytes.  Lengths must have been validated.
 void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hq,
                         int64_t cus, PrefillPlan *p);
 

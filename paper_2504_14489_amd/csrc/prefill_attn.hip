@@ -169,20 +169,26 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     p->piece_tiles = 0;
     p->split_bytes = 0;
     p->rows = 0;
-    int max_nt = 0;
-    int64_t units = 0, tiles = 0;  // 128-row query blocks x kv heads, and their key tiles
+    p->body = kBodyPlain;
+    int max_nt = 0, min_nt = INT32_MAX;
+    int64_t units = 0, tiles = 0, units8 = 0, tiles8 = 0;  // 128- and 256-row query blocks x kv heads, their key tiles
     for (int32_t b = 0; b < batch; ++b) {
         const int n = h_new_lens[b], r = h_prefix_lens[b];
         p->rows += n;
-        const int64_t blocks = (static_cast<int64_t>(n) * p->group + 127) / 128;
+        const int64_t blocks = (static_cast<int64_t>(n) * p->group + 127) / 128, blocks8 = (blocks + 1) / 2;
         if (blocks == 0) continue;
         const int first = prefill_block_tiles(r, n, 0, 128, p->group), last = (r + n + 63) / 64;
         max_nt = std::max(max_nt, last);
+        min_nt = std::min(min_nt, first);
         units += blocks;
         tiles += blocks * (first + last) / 2;
+        units8 += blocks8;
+        tiles8 += blocks8 * (prefill_block_tiles(r, n, 0, 256, p->group) + last) / 2;
     }
     units *= p->hkv;
     tiles *= p->hkv;
+    units8 *= p->hkv;
+    tiles8 *= p->hkv;
     if (p->waves != 4 || units == 0) return;
     const auto bytes_for = [&](int pieces) {
         return pieces > 1 ? static_cast<size_t>(pieces) * p->rows * hq * (kHeadDim * 4 + 8) : 0;
@@ -193,32 +199,52 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
         p->split_bytes = bytes_for(p->pieces);
         return;
     }
-    // The cheapest number of pieces of the longest block, in microseconds.  A
-    // work-group takes 1.65 us per two tiles and 6 us around them (measured
-    // with clock stamps on the whole GPU: 1.60-1.72 and 5.4-6.1 over a 2048-
-    // and a 1000-token chunk and a one-kv-head shard).  Up to one work-group
-    // per CU the call lasts as long as the longest piece, past that as the
-    // work's even share and half a piece.  The merge is a launch (2 us) and a
-    // pass over the partials, written and read at about 4 TB/s.  With fewer
-    // blocks than CUs, or with fewer than two per CU and blocks of 96 tiles or
-    // more, whole blocks always lose (or tie) and are not considered; two
-    // blocks per CU and more even out by themselves and are never cut.
-    const double kTwoTiles = 1.65, kAround = 6.0, kMergeLaunch = 2.0, kMergeBytesPerUs = 4e6;
-    const bool must_cut = units < cus || (units < 2 * cus && max_nt >= 96);
+    // The cheapest body, and for dual blocks number of pieces of the longest
+    // block, by their time in microseconds, fitted to 40 calls of 1 to 16
+    // sequences, 1 to 4096 new tokens over 0 to 8000, groups of 1 to 8, on 96
+    // to 256 CUs (each body and 1, 2 and 4 pieces measured on each; the choice
+    // is within 8% of the best measured on all of them).  A work-group takes
+    // `around` and `per` for each key tile.  With no more work-groups than
+    // slots the call lasts as long as its longest one; past that as the even
+    // share of the work and half the lightest one, dispatched last.
+    struct Cost {
+        double around, per;
+    };
+    const Cost kAlone4{5.1, units <= cus ? 1.2 : 1.35}, kShared4{5.1, 2.0}, kDual{6.8, 0.75}, kFullDual{7.0, 0.79}, kAlone8{6.5, 1.45},
+        kFull8{7.0, 1.6};
+    const auto time_of = [&](int64_t n, double n_tiles, double longest, double lightest, int64_t slots, Cost alone,
+                             Cost full) {
+        const double one = alone.around + alone.per * longest;
+        if (n <= cus) return one;
+        return std::max(one, (full.around * n + full.per * n_tiles) / slots +
+                                 0.5 * (full.around + full.per * lightest) * (n > slots));
+    };
+    const double us4 = time_of(units, tiles, max_nt, min_nt, 2 * cus, kAlone4, kShared4);
+    const double us8 = time_of(units8, tiles8, max_nt, min_nt, cus, kAlone8, kFull8);
+    // Pieces: partials are written and read at about 4 TB/s for the rows of
+    // blocks longer than a piece, in a second launch (2 us).  Two blocks per CU
+    // and more even out by themselves and are never cut; fewer, of 96 tiles and
+    // more, always.
+    const bool must_cut = units < 2 * cus && max_nt >= 96;
     double best = INFINITY;
     int best_pt = 0;
     for (int k = must_cut ? 2 : 1; k <= (units < 2 * cus ? kPrefillMaxPieces : 1); ++k) {
         const int pt = std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k);
-        const double longest = kAround + kTwoTiles * ((pt + 1) / 2);
-        double us = longest;
-        if (units * k > cus)
-            us = static_cast<double>(kAround * units * k + kTwoTiles * tiles / 2) / cus + 0.5 * longest;
-        if (k > 1) us += kMergeLaunch + 2.0 * bytes_for(k) / kMergeBytesPerUs;
+        if (k > 1 && pt >= max_nt) break;
+        const double cut = k == 1 ? 0.0 : std::min(1.0, static_cast<double>(max_nt - pt) / (max_nt - min_nt + 1));
+        double us = time_of(units * k, tiles, pt, k == 1 ? min_nt : 0.5 * pt, cus, kDual, kFullDual);
+        if (k > 1) us += 2.0 + cut * 2.0 * bytes_for(k) / 4e6;
         if (us < best) {
             best = us;
             best_pt = k > 1 ? pt : 0;
         }
     }
+    if (!must_cut && us8 < std::min(best, us4)) {
+        p->body = kBodyEight;
+        return;
+    }
+    if (!must_cut && us4 < best) return;
+    p->body = kBodyDual;
     if (best_pt == 0) return;
     p->piece_tiles = best_pt;
     p->pieces = prefill_pieces(max_nt, best_pt, kPrefillMaxPieces);
@@ -290,6 +316,24 @@ mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_smal
                          allow_small, p);
     p->table_in_lds = max_pages <= kBtCache;
     p->scale_log2 = shape->scale * kLog2e;
+    // Ordering over the batch costs a work-group 1.3 us to find its block: worth
+    // it when blocks are long against the rounds of work-groups (an eighth of
+    // the longest one's time), not for a launch that is resident at once.
+    if (p->order == kSorted) {
+        int64_t max_n_rows = 0, longest = 0;
+        for (int32_t b = 0; b < a->batch; ++b) {
+            max_n_rows = std::max<int64_t>(max_n_rows, static_cast<int64_t>(a->h_new_lens[b]) * p->group);
+            if (a->h_new_lens[b] > 0)
+                longest = std::max<int64_t>(longest, (a->h_prefix_lens[b] + a->h_new_lens[b] + 63) / 64);
+        }
+        const int64_t rows = 32 * p->waves, slots = p->waves == 8 ? cus : 2 * cus;
+        const int64_t grid = (max_n_rows + rows - 1) / rows * p->hkv * a->batch;
+        if (grid <= slots || 1.6 * longest * slots < 8 * 1.3 * grid) {
+            p->order = p->paired ? kPairs : kPerSequence;
+            p->grid_x = p->gx;
+            p->grid_y = a->batch;
+        }
+    }
     if (p->grid_x > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     return MW_OK;
 }
@@ -347,6 +391,25 @@ void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int
 
 }  // namespace mw
 
+// One launch of 8- or 4-wave blocks as planned by prefill_prepare.
+static mw_status launch_plain(const mw_prefill_args &a, const PrefillPlan &pl, hipStream_t s, mw_timing *timing) {
+    mw_status st = timing_begin(timing, s);
+    if (st != MW_OK) return st;
+    if (pl.grid_x > 0) {
+        auto kernel = pl.waves == 4 ? (pl.table_in_lds ? k_prefill_attn<true, 4> : k_prefill_attn<false, 4>)
+                                    : (pl.table_in_lds ? k_prefill_attn<true, 8> : k_prefill_attn<false, 8>);
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.grid_x), pl.grid_y), dim3(64 * pl.waves), 0, s,
+                           a.pool->k, a.pool->v, static_cast<const uint16_t *>(a.d_q),
+                           static_cast<uint16_t *>(a.d_out), a.d_qo_indptr, a.d_prefix_lens, a.d_block_table,
+                           a.bt_stride, a.batch, pl.hkv, pl.group, a.pool->desc.num_pages, pl.scale_log2, pl.order);
+        st = check_launch("k_prefill_attn");
+        if (st != MW_OK) return st;
+    }
+    st = timing_kernel_done(timing, s);
+    timing_end(timing);
+    return st;
+}
+
 extern "C" mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape *shape, int32_t batch,
                                      const int32_t *h_new_lens, const int32_t *h_prefix_lens,
                                      const int32_t *d_qo_indptr, const int32_t *d_prefix_lens,
@@ -360,21 +423,7 @@ extern "C" mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape
     PrefillPlan pl;
     mw_status st = prefill_prepare(&a, stream_cus(s), true, &pl, who);
     if (st != MW_OK) return st;
-    st = timing_begin(timing, s);
-    if (st != MW_OK) return st;
-    if (pl.grid_x > 0) {
-        auto kernel = pl.waves == 4 ? (pl.table_in_lds ? k_prefill_attn<true, 4> : k_prefill_attn<false, 4>)
-                                    : (pl.table_in_lds ? k_prefill_attn<true, 8> : k_prefill_attn<false, 8>);
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.grid_x), pl.grid_y), dim3(64 * pl.waves), 0, s,
-                           pool->k, pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out),
-                           d_qo_indptr, d_prefix_lens, d_block_table, bt_stride, batch, pl.hkv, pl.group,
-                           pool->desc.num_pages, pl.scale_log2, pl.order);
-        st = check_launch("k_prefill_attn");
-        if (st != MW_OK) return st;
-    }
-    st = timing_kernel_done(timing, s);
-    timing_end(timing);
-    return st;
+    return launch_plain(a, pl, s, timing);
 }
 
 extern "C" mw_status mw_prefill_workspace_size(const mw_attn_shape *shape, int32_t batch, const int32_t *h_new_lens,
@@ -417,8 +466,7 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
     if (st != MW_OK) return st;
     const int64_t n_big = prefill_big_units(batch, h_new_lens, h_prefix_lens, cus, pl);
     if ((pl.waves == 8 && n_big == 0) || pl.gx == 0)
-        return mw_prefill_attn(pool, shape, batch, h_new_lens, h_prefix_lens, d_qo_indptr, d_prefix_lens,
-                               d_block_table, bt_stride, d_q, d_out, stream, timing);
+        return launch_plain(a, pl, s, timing);
     if (n_big > 0) {
         const int64_t units = pl.blocks * pl.hkv;
         st = timing_begin(timing, s);
@@ -435,6 +483,13 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
         return st;
     }
     prefill_split_plan(batch, h_new_lens, h_prefix_lens, shape->num_q_heads, cus, &pl);
+    if (pl.body != kBodyDual) {
+        if (pl.body == kBodyEight) {
+            st = prefill_prepare(&a, cus, false, &pl, who);
+            if (st != MW_OK) return st;
+        }
+        return launch_plain(a, pl, s, timing);
+    }
     const bool cut = pl.pieces > 1;
     if (cut && (!d_workspace || !aligned16(d_workspace) || workspace_bytes < pl.split_bytes))
         return fail(MW_ERR_INVALID_ARG, "%s: the split needs a 16-byte aligned workspace of %zu bytes (got %zu)",
