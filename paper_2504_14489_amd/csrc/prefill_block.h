@@ -248,6 +248,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
     static_assert(!kSplit || kDual, "the key-range split runs dual blocks");
     constexpr int kBR = kDual ? 128 : 32 * NW;  // query rows per block
     constexpr int kNT = 64 * NW;        // threads
+    constexpr bool kStageQ = kDual || NW == 4;  // Q through LDS: 256 rows do not fit beside the first tile
     constexpr int kRows = 64 / NW;      // tile rows (keys) each wave loads
     constexpr int kJ = kRows / 4;       // 1-KB loads per wave per K (or V) tile
     constexpr int kEvery = 8 / kJ;      // QK MFMAs between two of this wave's loads
@@ -546,9 +547,36 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         } else {
             first_tile(flag<NW == 4>());
         }
-        // Q^T operand, all 8 dim-steps (k = 16*kb + 8*g + e).  Rows past the
-        // sequence's end take the last row's: their results are not stored
-        {
+        // Q^T operand, all 8 dim-steps (k = 16*kb + 8*g + e).  The rows go
+        // through tile buffers that are free until tile 1, a wave's 8 KiB in
+        // the K operand's layout, and rows past the sequence's end are zeros
+        // (their results are not stored).  Loaded straight into registers every
+        // lane's 16 bytes lie in another row, so a request touches 32 rows and
+        // both groups of a dual block ask for the same ones: the CU's 64
+        // requests took about 1 us of a work-group's start; whole rows, once
+        // each, are 32 requests of four rows.  Kernel time, direct / through
+        // LDS: one prompt of 256 tokens (32/8 heads) 9.7 / 8.6 us, of 768
+        // 15.8 / 14.6, of 2048 41.6 / 40.0; 2048 tokens of 8/1 heads on 96 CUs
+        // 28.6 / 26.9.  The 8-wave body keeps the direct loads: staging what
+        // fits (six waves' rows) was 1% slower on 16384-token prompts.
+        [[maybe_unused]] uint16_t *const sq = kDual ? s_v + (lw < 2 ? 1 : 3) * TILE + (lw & 1) * (TILE / 2)
+                                                    : (wave < 2 ? s_k : s_v) + TILE + (wave & 1) * (TILE / 2);
+        if constexpr (kStageQ) {
+            const uint16_t *qp = q + (static_cast<size_t>(row0 + min(pos0, n - 1)) * hq + kvh * group) * kHeadDim;
+            // bytes from head 0 of the group at position pos0 to the sequence's
+            // end (a wave's rows lie within 33 positions)
+            const int bytes = 2 * kHeadDim * max(min(n - pos0, 33) * hq - kvh * group, 0);
+            const __amdgpu_buffer_rsrc_t rq =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(qp), 0, bytes, kBufferFormat);
+            const int first = kDual ? 16 * grp : 0;  // each group loads half of the rows both use
+#pragma unroll
+            for (int j = 0; j < (kDual ? 4 : 8); ++j) {
+                const int row = first + 4 * j + (lane >> 4), oo = head0 + row, dp = over_group(oo);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rq, reinterpret_cast<lds_void *>(reinterpret_cast<uintptr_t>(sq + (first + 4 * j) * ROW)), 16,
+                    2 * ((dp * hq + oo - dp * group) * kHeadDim + 8 * ((lane & 15) ^ swz(row))), 0, 0, 0);
+            }
+        } else {  // (here rows past the end take the last position's)
             const uint16_t *qp =
                 q + (static_cast<size_t>(row0 + min(pos, n - 1)) * hq + kvh * group + hrow) * kHeadDim + 8 * g;
 #pragma unroll
@@ -570,7 +598,15 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 s_bt[i - pbase] = btrow[i];
             __syncthreads();
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        if constexpr (kStageQ)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        [[maybe_unused]] auto read_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 8; ++kb)
+                qop[kb] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(sq) + (koff ^ (32 * kb)));
+        };
         if constexpr (kDual) {  // V(0) and K(1), waited for at the end of M(0)
             const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_0), rk = page_rsrc(kpool, ref_1);
 #pragma unroll
@@ -578,8 +614,17 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 page_load_full(rv, sv, j);
                 page_load_full(rk, sk + TILE, j);
             }
+            wg_barrier();
+            // (read by the end of phase 1 at the latest; V(1) lands here from phase 2)
+            read_q();
+        } else {
+            // the wave's own rows, out of the buffers before tile 1's loads
+            if constexpr (kStageQ) {
+                read_q();
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+            wg_barrier();
         }
-        wg_barrier();
 
         if constexpr (kDual) {
             // As the 8-wave body below, each group runs M(0) S(0) M(1) ..
