@@ -371,8 +371,10 @@ def roofline_entries(b, res):
     n_launch = len(b.chunks)
     pre_ms = res["mux"]["prefill_kernel_ms"] / n_launch
     dec_ms = res["mux"]["decode_kernel_ms"]
-    split = res["mux"]["prefill_kernels"] > 1   # key-range split: split + merge kernels per call
-    pre = {"kernel": "k_prefill_split+k_prefill_merge" if split else "k_prefill_attn", "bound": "mfma",
+    # a call of one launch is listed under the plain kernel whichever body the
+    # plan took; a key-range split is two
+    split = res["mux"]["prefill_kernels"] > 1
+    pre = {"kernel": "k_prefill_dual+k_prefill_merge" if split else "k_prefill_attn", "bound": "mfma",
            "unit": "TFLOP/s",
            "achieved": b.pre_flop / n_launch / (pre_ms * 1e-3) / 1e12, "peak": BF16_PEAK_TFLOPS,
            "work_per_launch": b.pre_flop / n_launch, "work_unit": "FLOP", "kernel_ms": pre_ms,

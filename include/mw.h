@@ -252,11 +252,11 @@ mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape *shape, in
 
 /* Prefill with split key ranges for grids too small to fill the stream's CUs
  * with 8-wave work-groups on 256 query rows each (a lone prompt on the whole
- * device, a tensor-parallel head shard on a partition).  Such a call runs
- * blocks of 128 rows whose key tiles the two halves of a work-group share,
- * merged inside it.  Where whole blocks would still leave CUs idle or end
+ * device, a tensor-parallel head shard on a partition).  Such a call runs, where
+ * a cost model finds them faster, blocks of 128 rows whose key tiles the two
+ * halves of a work-group share, merged inside it.  Where whole blocks would still leave CUs idle or end
  * unevenly, each block's key range is also cut into up to 8 equal pieces (the
- * number by a cost model): each piece computes the partial softmax state
+ * number by the same model): each piece computes the partial softmax state
  * (reference maximum m, row sum l, unnormalised output) of its keys into the
  * workspace, and a second kernel merges the pieces of every split block with
  * the log-sum-exp identity (the decode combine's merge; Table

@@ -21,7 +21,7 @@ mw_status fail(mw_status st, const char *fmt, ...) __attribute__((format(printf,
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Key-range split of the prefill query blocks of the 4-wave kernel: a block
+// Key-range split of the prefill query blocks of the dual kernel: a block
 // whose causal key range spans nt tiles of 64 keys is cut into this many
 // pieces, piece i covering tiles [i nt / k, (i + 1) nt / k).  With
 // piece_tiles >= 4 every cut lies at least three tiles before the block's end,

@@ -203,17 +203,17 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     // block, by their time in microseconds, fitted to 40 calls of 1 to 16
     // sequences, 1 to 4096 new tokens over 0 to 8000, groups of 1 to 8, on 96
     // to 256 CUs (each body and 1, 2 and 4 pieces measured on each; the choice
-    // is within 8% of the best measured on all of them; fitted before the
-    // 128-row bodies' Q went through LDS, which takes 0.5 to 1.1 us off both
-    // alike).  A work-group takes
-    // `around` and `per` for each key tile.  With no more work-groups than
-    // slots the call lasts as long as its longest one; past that as the even
-    // share of the work and half the lightest one, dispatched last.
+    // is within 8% of the best measured on all of them).  The fit dates from
+    // before the 128-row bodies took Q through LDS, which made both alike 0.5
+    // to 1.1 us faster.  A work-group takes `around` and `per` for each key
+    // tile.  With no more work-groups than slots the call lasts as long as its
+    // longest one; past that as the even share of the work and half the
+    // lightest one, dispatched last.
     struct Cost {
         double around, per;
     };
-    const Cost kAlone4{5.1, units <= cus ? 1.2 : 1.35}, kShared4{5.1, 2.0}, kDual{6.8, 0.75}, kFullDual{7.0, 0.79}, kAlone8{6.5, 1.45},
-        kFull8{7.0, 1.6};
+    const Cost kAlone4{5.1, units <= cus ? 1.2 : 1.35}, kShared4{5.1, 2.0}, kDual{6.8, 0.75}, kFullDual{7.0, 0.79},
+        kAlone8{6.5, 1.45}, kFull8{7.0, 1.6};
     const auto time_of = [&](int64_t n, double n_tiles, double longest, double lightest, int64_t slots, Cost alone,
                              Cost full) {
         const double one = alone.around + alone.per * longest;
