@@ -55,6 +55,7 @@
 #include <type_traits>
 
 #include "mw_internal.h"
+#include "prefill_layout.h"
 
 namespace {
 namespace pf {
@@ -246,6 +247,8 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
     static_assert(NW == 8 || NW == 4, "8 or 4 waves");
     static_assert(!kDual || NW == 8, "two groups of four waves");
     static_assert(!kSplit || kDual, "the key-range split runs dual blocks");
+    static_assert(kDualBufBytes == 2 * TILE * sizeof(uint16_t) && kDualTableBytes == kBtCache * sizeof(int32_t),
+                  "buffers of a dual block");
     constexpr int kBR = kDual ? 128 : 32 * NW;  // query rows per block
     constexpr int kNT = 64 * NW;        // threads
     constexpr bool kStageQ = kDual || NW == 4;  // Q through LDS: 256 rows do not fit beside the first tile
@@ -794,12 +797,13 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         if constexpr (kDual) {
             // ---- merge the groups: waves w and w + 4 hold the same rows over
             // different keys.  Group 0 finishes dims 0..63 and group 1 dims
-            // 64..127: each hands the other half of its O (8 KiB per wave, in
-            // its own K buffers, as float4 per lane) with its (m, l).
+            // 64..127: each hands the other half of its O (in its own K
+            // buffers, as float4 per lane) with its (m, l) (in the table copy,
+            // which no wave reads past the loop's last barrier).
             const float lt = l_run + __shfl_xor(l_run, 32);
             f32x16 keep[2];
             {
-                float4 *give = reinterpret_cast<float4 *>(sk) + lw * 512;
+                float4 *give = reinterpret_cast<float4 *>(reinterpret_cast<char *>(sk) + dual_hand_over(lw));
 #pragma unroll
                 for (int db = 0; db < 2; ++db) {
                     const f32x16 gv = grp == 0 ? oacc[2 + db] : oacc[db];
@@ -809,18 +813,21 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                         give[(4 * db + i4) * 64 + lane] =
                             make_float4(gv[4 * i4], gv[4 * i4 + 1], gv[4 * i4 + 2], gv[4 * i4 + 3]);
                 }
-                if (g == 0) reinterpret_cast<float2 *>(sv)[lw * 32 + l32] = make_float2(m_run, lt);
+                if (g == 0)
+                    *reinterpret_cast<float2 *>(reinterpret_cast<char *>(s_bt) + dual_ml(grp, lw * 32 + l32)) =
+                        make_float2(m_run, lt);
             }
             __syncthreads();
             float inv, m_all, l_all;
             {
-                const uint16_t *pk = s_k + (1 - grp) * 2 * TILE, *pv = s_v + (1 - grp) * 2 * TILE;
-                const float2 ml = reinterpret_cast<const float2 *>(pv)[lw * 32 + l32];
+                const char *pk = reinterpret_cast<const char *>(s_k + (1 - grp) * 2 * TILE);
+                const float2 ml = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s_bt) +
+                                                                    dual_ml(1 - grp, lw * 32 + l32));
                 m_all = vmax(m_run, ml.x);
                 const float wa = __builtin_amdgcn_exp2f(m_run - m_all), wb = __builtin_amdgcn_exp2f(ml.x - m_all);
                 l_all = wa * lt + wb * ml.y;
                 inv = 1.f / l_all;
-                const float4 *got = reinterpret_cast<const float4 *>(pk) + lw * 512;
+                const float4 *got = reinterpret_cast<const float4 *>(pk + dual_hand_over(lw));
 #pragma unroll
                 for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -832,18 +839,19 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                         keep[db][4 * i4 + 3] = wa * keep[db][4 * i4 + 3] + wb * v.w;
                     }
             }
-            // the wave's 32 x 64 half tile, staged in the rest of its V buffers
-            // (past the (m, l) words) so that stores write whole half rows
-            char *st = reinterpret_cast<char *>(sv) + 1024 + lw * (32 * 256);
+            // the wave's 32 x 64 half tile, staged in its group's V buffers so
+            // that stores write whole half rows.  Nothing else of the merge lies
+            // there, so no barrier is needed: the waves still merging read the
+            // other group's K buffers and the table copy.
+            char *st = reinterpret_cast<char *>(sv) + dual_stage(lw);
             if (kSplit && n_pieces > 1) {
-                // this piece's partial: (m, l) and the unnormalised O, fp32;
-                // row q holds its 16-byte chunk c at chunk c ^ (q % 16)
+                // this piece's partial: (m, l) and the unnormalised O, fp32
 #pragma unroll
                 for (int db = 0; db < 2; ++db)
 #pragma unroll
                     for (int i4 = 0; i4 < 4; ++i4) {
                         const int c = 8 * db + 2 * i4 + g;
-                        *reinterpret_cast<float4 *>(st + l32 * 256 + 16 * (c ^ (l32 & 15))) =
+                        *reinterpret_cast<float4 *>(st + dual_stage_f32(l32, c)) =
                             make_float4(keep[db][4 * i4], keep[db][4 * i4 + 1], keep[db][4 * i4 + 2],
                                         keep[db][4 * i4 + 3]);
                     }
@@ -851,7 +859,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int row = 4 * j + (lane >> 4), c = lane & 15;
-                    const float4 v = *reinterpret_cast<const float4 *>(st + row * 256 + 16 * (c ^ (row & 15)));
+                    const float4 v = *reinterpret_cast<const float4 *>(st + dual_stage_f32(row, c));
                     const int oo = head0 + row, dp = over_group(oo);
                     const int h = kvh * group + oo - dp * group;
                     if (pos0 + dp < n)
@@ -861,20 +869,20 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 if (grp == 0 && g == 0 && pos < n)
                     sp.ml[(slot + pos) * hq + kvh * group + hrow] = make_float2(m_all, l_all);
             } else {
-                // normalised bf16; row q holds its 16-byte chunk c at c ^ (q % 8)
+                // normalised bf16
 #pragma unroll
                 for (int db = 0; db < 2; ++db)
 #pragma unroll
                     for (int i4 = 0; i4 < 4; ++i4) {
                         const int c = 4 * db + i4;
-                        *reinterpret_cast<uint2 *>(st + l32 * 128 + 16 * (c ^ (l32 & 7)) + 8 * g) =
+                        *reinterpret_cast<uint2 *>(st + dual_stage_bf16(l32, c) + 8 * g) =
                             make_uint2(cvt2(keep[db][4 * i4 + 0] * inv, keep[db][4 * i4 + 1] * inv),
                                        cvt2(keep[db][4 * i4 + 2] * inv, keep[db][4 * i4 + 3] * inv));
                     }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int row = 8 * j + (lane >> 3), c = lane & 7;
-                    const uint4 v = *reinterpret_cast<const uint4 *>(st + row * 128 + 16 * (c ^ (row & 7)));
+                    const uint4 v = *reinterpret_cast<const uint4 *>(st + dual_stage_bf16(row, c));
                     const int oo = head0 + row, dp = over_group(oo);
                     const int h = kvh * group + oo - dp * group;
                     if (pos0 + dp < n)

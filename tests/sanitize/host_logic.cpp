@@ -1,7 +1,7 @@
 // The library's host logic on randomised inputs, for a build with
 // AddressSanitizer and UndefinedBehaviorSanitizer: the decode and prefill
-// launch planners, the page allocator and the estimator (with the prefill
-// launch simulation).  Nothing here
+// launch planners, the LDS regions of the dual prefill blocks' merge, the page
+// allocator and the estimator (with the prefill launch simulation).  Nothing here
 // launches a kernel or touches a GPU: the device pointers are host addresses
 // the planners only check for alignment.  Prints "ok" when every check holds.
 #include <cstdio>
@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "mw_internal.h"
+#include "prefill_layout.h"
 
 namespace {
 
@@ -122,6 +123,60 @@ void planners() {
     }
 }
 
+// The merge of a dual block's two wave groups: no two of the O halves handed
+// over, the (m, l) words and the staged rows (fp32 and bf16) may share a byte or
+// leave their buffers, for there is no barrier between one wave's staging and
+// another's reads.  Counts the bytes that do; ml_at and stage_at place the words
+// (in the group's V buffers if ml_in_v, else in the table copy) and the rows.
+template <class Ml, class Stage>
+int dual_merge_clashes(bool ml_in_v, Ml ml_at, Stage stage_at) {
+    int bad = 0;
+    std::vector<uint8_t> k[2], v[2], table(mw::kDualTableBytes, 0);
+    for (int g = 0; g < 2; ++g) k[g].assign(mw::kDualBufBytes, 0), v[g].assign(mw::kDualBufBytes, 0);
+    // bytes past a group's buffers lie in the next group's, or outside
+    auto take = [&](std::vector<uint8_t>(&buf)[2], int g, int at, int n, int mark) {
+        for (int i = at; i < at + n; ++i) {
+            const int gg = g + i / mw::kDualBufBytes;
+            if (gg > 1) {
+                ++bad;
+                continue;
+            }
+            uint8_t &b = buf[gg][i % mw::kDualBufBytes];
+            if ((b && b != mark) || gg != g) ++bad;
+            b = static_cast<uint8_t>(mark);
+        }
+    };
+    for (int g = 0; g < 2; ++g)
+        for (int w = 0; w < 4; ++w) {
+            const int mark = 1 + 4 * g + w;
+            for (int lane = 0; lane < 64; ++lane)
+                for (int j = 0; j < 8; ++j) take(k, g, mw::dual_hand_over(w) + (j * 64 + lane) * 16, 16, mark);
+            for (int row = 0; row < 32; ++row) {
+                for (int c = 0; c < 16; ++c) take(v, g, stage_at(w) + mw::dual_stage_f32(row, c), 16, mark);
+                for (int c = 0; c < 8; ++c) take(v, g, stage_at(w) + mw::dual_stage_bf16(row, c), 16, mark);
+                const int at = ml_at(g, 32 * w + row);
+                for (int i = at; i < at + 8; ++i) {
+                    if (ml_in_v) {
+                        if (v[g][i]) ++bad;
+                        v[g][i] = 255;
+                    } else {
+                        if (i < 0 || i >= mw::kDualTableBytes || table[i]) ++bad;
+                        else table[i] = 1;
+                    }
+                }
+            }
+        }
+    return bad;
+}
+
+void dual_merge() {
+    check(dual_merge_clashes(false, mw::dual_ml, mw::dual_stage) == 0, "LDS regions of the dual merge", -1);
+    // the checker finds the words at the start of the V buffers and the rows
+    // 1 KiB behind them, whose last fp32 rows run over the end
+    check(dual_merge_clashes(true, [](int, int row) { return 8 * row; }, [](int w) { return 1024 + 8192 * w; }) > 0,
+          "a clash planted in the dual merge's regions", -1);
+}
+
 void allocator() {
     mw_kv_pool_desc desc{1000, 16, 2, 128};
     mw_kv_pool *pool = nullptr;
@@ -223,6 +278,7 @@ void estimator() {
 
 int main() {
     planners();
+    dual_merge();
     allocator();
     estimator();
     if (g_fail) return 1;
