@@ -56,6 +56,7 @@
 
 #include "mw_internal.h"
 #include "prefill_layout.h"
+#include "prefill_schedule.h"
 
 namespace {
 namespace pf {
@@ -610,17 +611,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             for (int kb = 0; kb < 8; ++kb)
                 qop[kb] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(sq) + (koff ^ (32 * kb)));
         };
-        if constexpr (kDual) {  // V(0) and K(1), waited for at the end of M(0)
-            const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_0), rk = page_rsrc(kpool, ref_1);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                page_load_full(rv, sv, j);
-                page_load_full(rk, sk + TILE, j);
-            }
-            wg_barrier();
-            // (read by the end of phase 1 at the latest; V(1) lands here from phase 2)
-            read_q();
-        } else {
+        if constexpr (!kDual) {
             // the wave's own rows, out of the buffers before tile 1's loads
             if constexpr (kStageQ) {
                 read_q();
@@ -630,15 +621,10 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         }
 
         if constexpr (kDual) {
-            // As the 8-wave body below, each group runs M(0) S(0) M(1) ..
-            // S(own-1) M(own) over its own tiles, with its own K and V buffers,
-            // group 1 one phase after group 0, so that one group's matrix phase
-            // runs beside the other's softmax.  A group loads its K(u+2) and
-            // V(u+1) at the start of its softmax S(u), into the buffers that
-            // M(u) was the last to read, and waits for them at the end of
-            // M(u+1): a period and a half before their first use in M(u+2).
-            const int total = t_hi - t_lo, periods = (total + 1) / 2;
-            const int own = grp == 0 ? periods : total / 2;  // tiles of this group
+            // Two wave groups on alternate tiles (dual_schedule has the order of
+            // their steps, and why no buffer is written while it is read).
+            const int total = t_hi - t_lo;
+            const int own = (total + 1 - grp) / 2;  // tiles of this group
             const auto tile = [&](int u) __attribute__((always_inline)) { return t_lo + 2 * u + grp; };
             // page lw of the group's tile u, its entry read a period ahead
             auto table_entry = [&](int u) __attribute__((always_inline)) {
@@ -649,47 +635,54 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 else
                     return ok ? (p - pbase < kBtCache ? s_bt[p - pbase] : btrow[p]) : -1;
             };
-            int pg_n = kTableInLds ? table_entry(2) : 0;
-            PageRef ref_v = ref_1;  // page lw of tile u + 1, whose V is loaded in S(u)
-            auto period_loads = [&](int u) __attribute__((always_inline)) {
-                PageRef ref_k;
-                if constexpr (kTableInLds) {
-                    ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(pg_n));
-                    pg_n = table_entry(u + 3);
-                } else {
-                    ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(table_entry(u + 2)));
+            int pg_n = 0;
+            PageRef ref_v = ref_1;  // page lw of tile u + 1, whose V is loaded in M(u + 1)
+            PageRef ref_k{0, 0};    // page lw of tile u + 2, whose K is loaded in S(u)
+            dual_schedule(grp, total, [&](auto kind, int u) __attribute__((always_inline)) {
+                constexpr DualStep what = decltype(kind)::value;
+                if constexpr (what == kDualFirstLoads) {
+                    const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_0), rk = page_rsrc(kpool, ref_1);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        page_load_full(rv, sv, j);
+                        page_load_full(rk, sk + TILE, j);
+                    }
+                } else if constexpr (what == kDualReadQ) {
+                    read_q();
+                    if constexpr (kTableInLds) pg_n = table_entry(2);
+                } else if constexpr (what == kDualBarrier) {
+                    wg_barrier();
+                } else if constexpr (what == kDualWaitAll) {
+                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+                } else if constexpr (what == kDualWaitOlder) {
+                    __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4)
+                } else if constexpr (what == kDualScores) {
+                    mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});
+                } else if constexpr (what == kDualSoftmax) {
+                    if constexpr (kTableInLds) {
+                        ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(pg_n));
+                        pg_n = table_entry(u + 3);
+                    } else {
+                        ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(table_entry(u + 2)));
+                    }
+                    // (no bytes past the group's last tile: the loads return zeros)
+                    const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, u + 2 < own ? ref_k : PageRef{0, 0});
+                    softmax_phase(tile(u), [&](int j) __attribute__((always_inline)) {
+                        if (j >= 4) page_load_full(rk, sk + (u & 1) * TILE, j - 4);
+                    });
+                } else if constexpr (what == kDualMatrix) {
+                    const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_v);
+                    mfma_phase(flag<true>(), flag<true>(), (u + 1) & 1, u & 1,
+                               [&](int j) __attribute__((always_inline)) {
+                                   page_load_full(rv, sv + ((u + 1) & 1) * TILE, j);
+                               });
+                    ref_v = ref_k;
+                } else if constexpr (what == kDualLastSoftmax) {
+                    softmax_phase(tile(u), [](int) {});
+                } else if constexpr (what == kDualLastMatrix) {
+                    mfma_phase(flag<true>(), flag<false>(), 0, u & 1, [](int) {});
                 }
-                // (no bytes past the group's last tile: the loads return zeros)
-                const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, u + 2 < own ? ref_k : PageRef{0, 0});
-                const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_v);
-                softmax_phase(tile(u), [&](int j) __attribute__((always_inline)) {
-                    if (j >= 4) page_load_full(rk, sk + (u & 1) * TILE, j - 4);
-                });
-                __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4): all but the K loads just issued
-                wg_barrier();
-                mfma_phase(flag<true>(), flag<true>(), (u + 1) & 1, u & 1, [&](int j) __attribute__((always_inline)) {
-                    page_load_full(rv, sv + ((u + 1) & 1) * TILE, j);
-                });
-                wg_barrier();
-                ref_v = ref_k;
-            };
-            auto vm_wait = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
-            if (grp == 1) wg_barrier();
-            if (own > 0) {
-                mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});
-                vm_wait();
-                wg_barrier();
-                for (int u = 0; u + 1 < own; ++u) {
-                    period_loads(u);
-                }
-                softmax_phase(tile(own - 1), [](int) {});
-                vm_wait();
-                wg_barrier();
-                mfma_phase(flag<true>(), flag<false>(), 0, (own - 1) & 1, [](int) {});
-                wg_barrier();
-            }
-            // 2 periods + 2 barriers in all for both groups
-            for (int i = own > 0 ? 2 * own + 1 : 0; i < 2 * periods + (grp == 0 ? 2 : 1); ++i) wg_barrier();
+            });
         } else if constexpr (NW == 8) {
             // Two groups of four waves (one wave of each on every SIMD), half a
             // period apart: while one group runs its matrix phase M(t) =
