@@ -339,6 +339,10 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
 
     // per-item state
     int nt = 0, qabs = 0, diag = 0;
+    // Key tiles that some row of the wave sees, from tile 0.  For the others of its
+    // block (past all of its rows) it only loads its pages and takes the barriers:
+    // their probabilities are 0, but 0 times a value that is not finite is not.
+    int nt_w = 0;
     int pos0 = 0, head0 = 0;   // position and head of the wave's first row
     uint4 qop[8];
     f32x16 oacc[4];
@@ -537,6 +541,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         const int hrow = o - dpos * group;  // and its head in the group
         qabs = r + pos;
         diag = r + pos0;                    // smallest query of the wave
+        nt_w = min(nt, (r + pos0 + over_group(head0 + 31)) / BN + 1);
         if (pass > 0) wg_barrier();  // the previous block's output staging is done
         PageRef ref_0{0, 0}, ref_1{0, 0};  // kDual: page lw of the group's first two tiles
         if constexpr (kDual) {
@@ -625,6 +630,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             // their steps, and why no buffer is written while it is read).
             const int total = t_hi - t_lo;
             const int own = (total + 1 - grp) / 2;  // tiles of this group
+            const int mine = min(own, max(0, (nt_w - t_lo - grp + 1) / 2));  // of them the wave's rows see
             const auto tile = [&](int u) __attribute__((always_inline)) { return t_lo + 2 * u + grp; };
             // page lw of the group's tile u, its entry read a period ahead
             auto table_entry = [&](int u) __attribute__((always_inline)) {
@@ -638,7 +644,18 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             int pg_n = 0;
             PageRef ref_v = ref_1;  // page lw of tile u + 1, whose V is loaded in M(u + 1)
             PageRef ref_k{0, 0};    // page lw of tile u + 2, whose K is loaded in S(u)
-            dual_schedule(grp, total, [&](auto kind, int u) __attribute__((always_inline)) {
+            // page lw of tile u + 2 (no bytes past the group's last tile: the loads
+            // return zeros)
+            const auto next_k = [&](int u) __attribute__((always_inline)) {
+                if constexpr (kTableInLds) {
+                    ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(pg_n));
+                    pg_n = table_entry(u + 3);
+                } else {
+                    ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(table_entry(u + 2)));
+                }
+                return page_rsrc(kpool, u + 2 < own ? ref_k : PageRef{0, 0});
+            };
+            dual_schedule(grp, total, mine, [&](auto kind, int u) __attribute__((always_inline)) {
                 constexpr DualStep what = decltype(kind)::value;
                 if constexpr (what == kDualFirstLoads) {
                     const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_0), rk = page_rsrc(kpool, ref_1);
@@ -659,14 +676,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 } else if constexpr (what == kDualScores) {
                     mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});
                 } else if constexpr (what == kDualSoftmax) {
-                    if constexpr (kTableInLds) {
-                        ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(pg_n));
-                        pg_n = table_entry(u + 3);
-                    } else {
-                        ref_k = page_ref(4 * tile(u + 2) + lw, __builtin_amdgcn_readfirstlane(table_entry(u + 2)));
-                    }
-                    // (no bytes past the group's last tile: the loads return zeros)
-                    const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, u + 2 < own ? ref_k : PageRef{0, 0});
+                    const __amdgpu_buffer_rsrc_t rk = next_k(u);
                     softmax_phase(tile(u), [&](int j) __attribute__((always_inline)) {
                         if (j >= 4) page_load_full(rk, sk + (u & 1) * TILE, j - 4);
                     });
@@ -676,6 +686,15 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                                [&](int j) __attribute__((always_inline)) {
                                    page_load_full(rv, sv + ((u + 1) & 1) * TILE, j);
                                });
+                    ref_v = ref_k;
+                } else if constexpr (what == kDualLoadK) {
+                    const __amdgpu_buffer_rsrc_t rk = next_k(u);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) page_load_full(rk, sk + (u & 1) * TILE, j);
+                } else if constexpr (what == kDualLoadV) {
+                    const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_v);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) page_load_full(rv, sv + ((u + 1) & 1) * TILE, j);
                     ref_v = ref_k;
                 } else if constexpr (what == kDualLastSoftmax) {
                     softmax_phase(tile(u), [](int) {});
@@ -748,7 +767,8 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
             mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});  // M(0): S(0) = K(0) Q^T
             if (grp == 1) vm_wait();
             wg_barrier();
-            for (int t = 0; t + 1 < nt; ++t) {
+            int t = 0;
+            for (; t + 1 < nt_w; ++t) {
                 if (grp == 1) period_loads(t + 1);
                 softmax_phase(t, [](int) {});
                 wg_barrier();
@@ -757,11 +777,20 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 if (grp == 1) vm_wait();
                 wg_barrier();
             }
-            // the last tile: softmax(nt-1), then M(nt) = O += V(nt-1)^T P(nt-1)^T
-            softmax_phase(nt - 1, [](int) {});
+            // the wave's last tile: softmax(t), then O += V(t)^T P(t)^T
+            if (grp == 1 && t + 1 < nt) period_loads(t + 1);
+            softmax_phase(t, [](int) {});
             wg_barrier();
-            mfma_phase(flag<true>(), flag<false>(), 0, (nt - 1) & 1, [](int) {});
+            mfma_phase(flag<true>(), flag<false>(), 0, t & 1, [](int) {});
+            if (grp == 1) vm_wait();
             wg_barrier();
+            // tiles that only other waves see
+            for (++t; t < nt; ++t) {
+                if (grp == 1 && t + 1 < nt) period_loads(t + 1);
+                wg_barrier();
+                if (grp == 1) vm_wait();
+                wg_barrier();
+            }
             if (grp == 0) wg_barrier();  // group 0's last phase: none of its own work
         } else
         // Tile t+1 is loaded (into the other buffer) while tile t is processed;
@@ -780,9 +809,14 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                         page_load(rv, dv, j - kJ);
                 }
             };
-            mfma_phase(flag<false>(), flag<true>(), t & 1, t & 1, load);
-            softmax_phase(t, [](int) {});
-            mfma_phase(flag<true>(), flag<false>(), t & 1, t & 1, [](int) {});
+            if (t < nt_w) {
+                mfma_phase(flag<false>(), flag<true>(), t & 1, t & 1, load);
+                softmax_phase(t, [](int) {});
+                mfma_phase(flag<true>(), flag<false>(), t & 1, t & 1, [](int) {});
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2 * kJ; ++j) load(j);
+            }
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's direct loads landed
             wg_barrier();
         }

@@ -18,8 +18,10 @@ enum DualStep {
     kDualScores,       // M(0): scores of tile 0 from K(0)
     kDualSoftmax,      // softmax of tile u; requests K(u + 2)
     kDualMatrix,       // M(u + 1): V(u) and K(u + 1); requests V(u + 1)
-    kDualLastSoftmax,  // softmax of the last tile u
-    kDualLastMatrix,   // V(u) of the last tile u
+    kDualLastSoftmax,  // softmax of the wave's last tile u
+    kDualLastMatrix,   // V(u) of the wave's last tile u
+    kDualLoadK,        // requests K(u + 2)
+    kDualLoadV,        // requests V(u + 1)
     kDualWaitAll,      // every load of the wave has landed
     kDualWaitOlder,    // all but the tile requested last
 };
@@ -31,12 +33,14 @@ enum DualStep {
 // that M(u) read; at its end the wave waits for all older loads, that is for
 // K(u+1) and V(u), which M(u+1) reads behind the next barrier; M(u+1) requests
 // V(u+1) into the buffer that M(u) read (V(1) into the one Q was read from, two
-// phases after every wave read it).  A group without tiles (one tile in all)
+// phases after every wave read it).  A wave takes part in the loads and barriers
+// of all of its group's tiles, but computes only on the first `mine` of them, those
+// its rows see.  A group without tiles (one tile in all)
 // reads nothing, but its first loads write zeros to its buffers: it waits for
 // them too, since the merge reuses the buffers.  Both groups pass the same
 // number of barriers: 2 ceil(total / 2) + 3.
 template <class Step>
-__host__ __device__ __forceinline__ void dual_schedule(int grp, int total, Step &&step) {
+__host__ __device__ __forceinline__ void dual_schedule(int grp, int total, int mine, Step &&step) {
     const auto run = [&](auto kind, int u) __attribute__((always_inline)) { step(kind, u); };
 #define MW_STEP(name, u) run(std::integral_constant<DualStep, name>{}, u)
     const int periods = (total + 1) / 2;
@@ -45,24 +49,45 @@ __host__ __device__ __forceinline__ void dual_schedule(int grp, int total, Step 
     MW_STEP(kDualBarrier, 0);
     MW_STEP(kDualReadQ, 0);
     if (grp == 1) MW_STEP(kDualBarrier, 0);
-    if (own > 0) {
+    int u = 0;
+    if (mine > 0) {
         MW_STEP(kDualScores, 0);
         MW_STEP(kDualWaitAll, 0);
         MW_STEP(kDualBarrier, 0);
-        for (int u = 0; u + 1 < own; ++u) {
+        for (; u + 1 < mine; ++u) {
             MW_STEP(kDualSoftmax, u);
             MW_STEP(kDualWaitOlder, u);
             MW_STEP(kDualBarrier, u);
             MW_STEP(kDualMatrix, u);
             MW_STEP(kDualBarrier, u);
         }
-        MW_STEP(kDualLastSoftmax, own - 1);
-        MW_STEP(kDualWaitAll, own - 1);
-        MW_STEP(kDualBarrier, own - 1);
-        MW_STEP(kDualLastMatrix, own - 1);
-        MW_STEP(kDualBarrier, own - 1);
+        if (mine == own) {
+            MW_STEP(kDualLastSoftmax, u);
+            MW_STEP(kDualWaitAll, u);
+        } else {
+            MW_STEP(kDualLoadK, u);
+            MW_STEP(kDualLastSoftmax, u);
+            MW_STEP(kDualWaitOlder, u);
+        }
+        MW_STEP(kDualBarrier, u);
+        MW_STEP(kDualLastMatrix, u);
+        if (mine < own) MW_STEP(kDualLoadV, u);
+        MW_STEP(kDualBarrier, u);
+        ++u;
     } else {
         MW_STEP(kDualWaitAll, 0);
+        if (own > 0) MW_STEP(kDualBarrier, 0);
+    }
+    for (; u < own; ++u) {  // tiles that only other waves see
+        if (u + 1 < own) {
+            MW_STEP(kDualLoadK, u);
+            MW_STEP(kDualWaitOlder, u);
+        } else {
+            MW_STEP(kDualWaitAll, u);
+        }
+        MW_STEP(kDualBarrier, u);
+        if (u + 1 < own) MW_STEP(kDualLoadV, u);
+        MW_STEP(kDualBarrier, u);
     }
     for (int i = own > 0 ? 2 * own + 1 : 0; i < 2 * periods + (grp == 0 ? 2 : 1); ++i) MW_STEP(kDualBarrier, 0);
 #undef MW_STEP

@@ -15,11 +15,16 @@ from tests.test_gpu_prefill import _varlen_setup
 pytestmark = pytest.mark.gpu
 
 
-def _run(hq, hkv, seqs, cus, seed):
+def _run(hq, hkv, seqs, cus, seed, bad_from=None):
     """The batch through the split-enabled and the plain entry point on the
     prefill stream of `cus` CUs (0: the whole GPU); every row of both against
-    the oracle."""
+    the oracle.  bad_from: the one sequence's values from this token on are NaN or
+    infinite, and only rows that may not depend on them are compared."""
     wls, k, v, bt, stride, q = _varlen_setup(seqs, hq, hkv, seed)
+    if bad_from is not None:
+        v = v.copy()
+        for tok in range(bad_from, sum(seqs[0])):
+            v[bt[0, tok // 16], :, tok % 16] = (0x7FC0, 0x7F80, 0xFF80)[tok % 3]  # bf16 NaN, inf, -inf
     dev = torch.device("cuda:0")
     t16 = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).to(dev)
     t32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(dev)
@@ -50,7 +55,13 @@ def _run(hq, hkv, seqs, cus, seed):
     for got, what in zip(outs, ("split-enabled", "plain")):
         row = 0
         for w, (r, n) in zip(wls, seqs):
-            if n:
+            if bad_from is not None:
+                # whole 64-position groups whose last key tile of 64 ends by bad_from
+                seen = max(i for i in range(0, n, 64) if -(-(r + i) // 64) * 64 <= bad_from)
+                assert seen > 0
+                ref = oracle.prefill(w.q_pre[r:r + seen], w.k_pool, w.v_pool, w.pre_bt, r)
+                assert_close(got[row:row + seen], ref, f"{what} hq={hq} hkv={hkv} r={r} n={n} cus={cus} bad values")
+            elif n:
                 ref = oracle.prefill(w.q_pre[r:r + n], w.k_pool, w.v_pool, w.pre_bt, r)
                 assert_close(got[row:row + n], ref, f"{what} hq={hq} hkv={hkv} r={r} n={n} cus={cus}")
             row += n
@@ -107,3 +118,15 @@ def test_prefill_batch_order(batch, cus):
 def test_prefill_last_round_in_halves(hq, hkv, seqs):
     say(f"prefill last round in halves hq={hq} hkv={hkv} {seqs}")
     _run(hq, hkv, seqs, 8, 1300)
+
+
+# values that are not finite from the second, third or last key tile on, which
+# lie past every position of the rows compared: a row's softmax gives them no
+# weight, and 0 times them must not reach the row through the other rows of its
+# block (up to 256 positions with one query head per kv head)
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (3, 1), (4, 2), (10, 2), (8, 2), (16, 1)])
+@pytest.mark.parametrize("r,n,bad_from", [(0, 256, 64), (64, 250, 192), (130, 300, 384), (0, 500, 448)])
+@pytest.mark.parametrize("cus", [0, 8])
+def test_prefill_later_values_not_finite(hq, hkv, r, n, bad_from, cus):
+    say(f"prefill later values not finite hq={hq} hkv={hkv} r={r} n={n} from {bad_from} cus={cus}")
+    _run(hq, hkv, [(r, n)], cus, 1700 + n, bad_from)
