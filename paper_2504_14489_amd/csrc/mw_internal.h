@@ -36,10 +36,12 @@ __host__ __device__ inline int prefill_pieces(int nt, int piece_tiles, int max_p
 }
 // Key tiles (64 keys) of query block q of a sequence with prefix r and n new
 // tokens: blocks of `block_rows` rows of n x group queries (by default 32
-// positions).
-__host__ __device__ inline int prefill_block_tiles(int r, int n, int q, int block_rows = 32, int group = 1) {
-    const int end = (q + 1) * block_rows < n * group ? (q + 1) * block_rows : n * group;
-    return (r + (end + group - 1) / group + 63) / 64;
+// positions).  T: the type of the row counts; 32 bits hold those of a call that
+// fits the device's memory, but not of every length a caller may ask a size for.
+template <class T = int>
+__host__ __device__ inline int prefill_block_tiles(T r, T n, T q, T block_rows = 32, T group = 1) {
+    const T end = (q + 1) * block_rows < n * group ? (q + 1) * block_rows : n * group;
+    return static_cast<int>((r + (end + group - 1) / group + 63) / 64);
 }
 
 // Number of CUs a stream's kernels may run on (its CU mask; all CUs of the

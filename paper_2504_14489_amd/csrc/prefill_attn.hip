@@ -177,13 +177,13 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
         p->rows += n;
         const int64_t blocks = (static_cast<int64_t>(n) * p->group + 127) / 128, blocks8 = (blocks + 1) / 2;
         if (blocks == 0) continue;
-        const int first = prefill_block_tiles(r, n, 0, 128, p->group), last = (r + n + 63) / 64;
+        const int first = prefill_block_tiles<int64_t>(r, n, 0, 128, p->group), last = static_cast<int>((static_cast<int64_t>(r) + n + 63) / 64);
         max_nt = std::max(max_nt, last);
         min_nt = std::min(min_nt, first);
         units += blocks;
         tiles += blocks * (first + last) / 2;
         units8 += blocks8;
-        tiles8 += blocks8 * (prefill_block_tiles(r, n, 0, 256, p->group) + last) / 2;
+        tiles8 += blocks8 * (prefill_block_tiles<int64_t>(r, n, 0, 256, p->group) + last) / 2;
     }
     units *= p->hkv;
     tiles *= p->hkv;
@@ -272,8 +272,8 @@ static int64_t prefill_big_units(int32_t batch, const int32_t *h_new_lens, const
     int most = 0, least = INT32_MAX;
     for (int32_t b = 0; b < batch; ++b) {
         if (h_new_lens[b] == 0) continue;
-        most = std::max(most, (h_prefix_lens[b] + h_new_lens[b] + 63) / 64);
-        least = std::min(least, prefill_block_tiles(h_prefix_lens[b], h_new_lens[b], 0, 256, p.group));
+        most = std::max(most, static_cast<int>((static_cast<int64_t>(h_prefix_lens[b]) + h_new_lens[b] + 63) / 64));
+        least = std::min(least, prefill_block_tiles<int64_t>(h_prefix_lens[b], h_new_lens[b], 0, 256, p.group));
     }
     if (2 * least < most) return 0;
     return whole / p.hkv * p.hkv;
@@ -326,7 +326,7 @@ mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_smal
         for (int32_t b = 0; b < a->batch; ++b) {
             max_n_rows = std::max<int64_t>(max_n_rows, static_cast<int64_t>(a->h_new_lens[b]) * p->group);
             if (a->h_new_lens[b] > 0)
-                longest = std::max<int64_t>(longest, (a->h_prefix_lens[b] + a->h_new_lens[b] + 63) / 64);
+                longest = std::max<int64_t>(longest, (static_cast<int64_t>(a->h_prefix_lens[b]) + a->h_new_lens[b] + 63) / 64);
         }
         const int64_t rows = 32 * p->waves, slots = p->waves == 8 ? cus : 2 * cus;
         const int64_t grid = (max_n_rows + rows - 1) / rows * p->hkv * a->batch;

@@ -124,6 +124,23 @@ void planners() {
     }
 }
 
+// Sizes of calls far past any pool: every length that the size call accepts, with
+// groups whose rows no longer fit 32 bits.
+void prefill_sizes() {
+    const int32_t most = INT32_MAX - 64;
+    for (int it = 0; it < 200; ++it) {
+        const int group = uniform(1, 64);
+        const mw_attn_shape shape{group, 1, 128, 0.0883883f};
+        const int32_t n = it < 8 ? most : uniform(1 << 24, most);
+        const int32_t r = n == most ? 0 : uniform(0, most - n);
+        const int32_t cus = it % 2 ? INT32_MAX : uniform(0, 1 << 30);
+        size_t bytes = 0;
+        check(mw_prefill_workspace_size(&shape, 1, &n, &r, cus, &bytes) == MW_OK, "size of a large call", it);
+        const size_t piece = static_cast<size_t>(n) * group * (mw::kHeadDim * 4 + 8);
+        check(bytes % piece == 0 && bytes / piece <= mw::kPrefillMaxPieces, "whole pieces of a large call", it);
+    }
+}
+
 // The merge of a dual block's two wave groups: no two of the O halves handed
 // over, the (m, l) words and the staged rows (fp32 and bf16) may share a byte or
 // leave their buffers, for there is no barrier between one wave's staging and
@@ -397,6 +414,7 @@ void estimator() {
 
 int main() {
     planners();
+    prefill_sizes();
     dual_merge();
     dual_order();
     allocator();
