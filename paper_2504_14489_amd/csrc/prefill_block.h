@@ -342,6 +342,10 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
     // Key tiles that some row of the wave sees, from tile 0.  For the others of its
     // block (past all of its rows) it only loads its pages and takes the barriers:
     // their probabilities are 0, but 0 times a value that is not finite is not.
+    // A wave past the sequence's rows has none: computing there on zeros only
+    // slowed the others down (14 sequences of 8 to 53 tokens over 12549 with 32/32
+    // heads took 732 us, now 558; 15 of 8 to 20 over 198 with 32/8 on 64 CUs 22.3,
+    // now 18.7).
     int nt_w = 0;
     int pos0 = 0, head0 = 0;   // position and head of the wave's first row
     uint4 qop[8];
@@ -541,7 +545,12 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         const int hrow = o - dpos * group;  // and its head in the group
         qabs = r + pos;
         diag = r + pos0;                    // smallest query of the wave
-        nt_w = min(nt, (r + pos0 + over_group(head0 + 31)) / BN + 1);
+        // (kept from the compiler, and the branches of the 8-wave loop hinted below:
+        // telling a wave without rows apart, it laid that loop out with jumps that
+        // made full blocks take up to 4% longer)
+        int last_key = wrow < rows ? r + pos0 + over_group(head0 + 31) : -BN;
+        asm volatile("" : "+s"(last_key));
+        nt_w = min(nt, last_key / BN + 1);
         if (pass > 0) wg_barrier();  // the previous block's output staging is done
         PageRef ref_0{0, 0}, ref_1{0, 0};  // kDual: page lw of the group's first two tiles
         if constexpr (kDual) {
@@ -745,16 +754,14 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 } else {
                     ref_k = page_ref(4 * (t + 1) + lw, __builtin_amdgcn_readfirstlane(table_entry(t + 1)));
                 }
-                if (t + 1 < nt) {
+                if (__builtin_expect(t + 1 < nt, 1)) {
                     const __amdgpu_buffer_rsrc_t rk = page_rsrc(kpool, ref_k);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) page_load_full(rk, s_k + ((t + 1) & 1) * TILE, j);
                 }
-                if (t < nt) {
-                    const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_v);
+                const __amdgpu_buffer_rsrc_t rv = page_rsrc(vpool, ref_v);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) page_load_full(rv, s_v + (t & 1) * TILE, j);
-                }
+                for (int j = 0; j < 4; ++j) page_load_full(rv, s_v + (t & 1) * TILE, j);
                 ref_v = ref_k;
             };
             auto vm_wait = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
@@ -764,28 +771,34 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 period_loads(0);
                 wg_barrier();
             }
-            mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});  // M(0): S(0) = K(0) Q^T
-            if (grp == 1) vm_wait();
-            wg_barrier();
             int t = 0;
-            for (; t + 1 < nt_w; ++t) {
-                if (grp == 1) period_loads(t + 1);
+            if (__builtin_expect(nt_w > 0, 1)) {
+                mfma_phase(flag<false>(), flag<true>(), 0, 0, [](int) {});  // M(0): S(0) = K(0) Q^T
+                if (grp == 1) vm_wait();
+                wg_barrier();
+                for (; __builtin_expect(t + 1 < nt_w, 1); ++t) {
+                    if (grp == 1) period_loads(t + 1);
+                    softmax_phase(t, [](int) {});
+                    wg_barrier();
+                    // M(t+1): O += V(t)^T P(t)^T, S(t+1) = K(t+1) Q^T
+                    mfma_phase(flag<true>(), flag<true>(), (t + 1) & 1, t & 1, [](int) {});
+                    if (grp == 1) vm_wait();
+                    wg_barrier();
+                }
+                // the wave's last tile: softmax(t), then O += V(t)^T P(t)^T
+                if (grp == 1 && t + 1 < nt) period_loads(t + 1);
                 softmax_phase(t, [](int) {});
                 wg_barrier();
-                // M(t+1): O += V(t)^T P(t)^T, S(t+1) = K(t+1) Q^T
-                mfma_phase(flag<true>(), flag<true>(), (t + 1) & 1, t & 1, [](int) {});
+                mfma_phase(flag<true>(), flag<false>(), 0, t & 1, [](int) {});
+                if (grp == 1) vm_wait();
+                wg_barrier();
+                ++t;
+            } else {
                 if (grp == 1) vm_wait();
                 wg_barrier();
             }
-            // the wave's last tile: softmax(t), then O += V(t)^T P(t)^T
-            if (grp == 1 && t + 1 < nt) period_loads(t + 1);
-            softmax_phase(t, [](int) {});
-            wg_barrier();
-            mfma_phase(flag<true>(), flag<false>(), 0, t & 1, [](int) {});
-            if (grp == 1) vm_wait();
-            wg_barrier();
             // tiles that only other waves see
-            for (++t; t < nt; ++t) {
+            for (; t < nt; ++t) {
                 if (grp == 1 && t + 1 < nt) period_loads(t + 1);
                 wg_barrier();
                 if (grp == 1) vm_wait();
