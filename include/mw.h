@@ -234,7 +234,9 @@ typedef struct {
     float scale;          /* softmax scale, usually 1/sqrt(head_dim)       */
 } mw_attn_shape;
 
-/* Causal prefill for `batch` sequences (varlen).
+/* Causal prefill for `batch` sequences (varlen), on blocks of 256 or 128 query
+ * rows and in the order over the batch that a cost model finds fastest for the
+ * lengths and the stream's CU count; results have the same bits on any.
  *   h_new_lens, h_prefix_lens host [batch]: n_b >= 0, r_b >= 0, with
  *       r_b + n_b <= bt_stride * page_size
  *   d_qo_indptr   device [batch+1]: rows of sequence b are
@@ -250,13 +252,15 @@ mw_status mw_prefill_attn(const mw_kv_pool *pool, const mw_attn_shape *shape, in
                           const int32_t *d_block_table, int32_t bt_stride, const void *d_q,
                           void *d_out, mw_stream stream, mw_timing *timing);
 
-/* Prefill with split key ranges for grids too small to fill the stream's CUs
- * with 8-wave work-groups on 256 query rows each (a lone prompt on the whole
- * device, a tensor-parallel head shard on a partition).  Such a call runs, where
- * a cost model finds them faster, blocks of 128 rows whose key tiles the two
- * halves of a work-group share, merged inside it.  Where whole blocks would still leave CUs idle or end
- * unevenly, each block's key range is also cut into up to 8 equal pieces (the
- * number by the same model): each piece computes the partial softmax state
+/* Prefill that may also share and split key ranges, for grids too small to fill
+ * the stream's CUs evenly with the work-groups of mw_prefill_attn (a lone prompt
+ * on the whole device, a tensor-parallel head shard on a partition).  Where a
+ * cost model finds them faster, a call runs blocks of 128 query rows whose key
+ * tiles the two halves of a work-group share, merged inside it.  Where whole
+ * blocks would still leave CUs idle or end unevenly, each block's key range is
+ * also cut into up to 8 equal pieces (the number by the same model; only where
+ * there are fewer than two blocks per CU, and fewer pairs of 256-row blocks than
+ * CUs): each piece computes the partial softmax state
  * (reference maximum m, row sum l, unnormalised output) of its keys into the
  * workspace, and a second kernel merges the pieces of every split block with
  * the log-sum-exp identity (the decode combine's merge; Table

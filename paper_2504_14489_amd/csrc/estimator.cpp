@@ -120,10 +120,11 @@ bool decode_terms(int32_t batch, const int32_t *lens, double out[4]) {
 
 // The modelled prefill launch on `cus` CUs, from the lengths: its path (0:
 // blocks of 64 positions, one work-group per CU; 1: blocks of 32 positions, two
-// per CU, cut into key ranges by model_split; the library's calls take their
-// 256-row and 128-row blocks on the same condition) and its load-imbalance
+// per CU, cut into key ranges by model_split), and its load-imbalance
 // factor: the latest CU's finishing time over the time of the same work spread
-// evenly over the CUs.  The work-groups are taken in dispatch order (grid x
+// evenly over the CUs.  It has the steps of a launch (rounds of work-groups,
+// the longest one), not the library's choice of bodies, orders and pieces, which
+// follows measured times call by call (prefill_attn.hip).  The work-groups are taken in dispatch order (grid x
 // fastest, then the sequence) and each goes to the CU slot that frees first,
 // all CUs' first slots before any second one; a work-group's work is its key
 // tiles (64 keys each), summed over the blocks it takes.  A CU that holds a
@@ -135,10 +136,42 @@ struct PrefillLaunch {
     double kappa;
 };
 
+// A modelled launch: blocks of 64 positions (8 waves) of up to four query heads
+// each unless their pairs would not even give every CU one, then of 32 (4 waves,
+// two work-groups per CU); in pairs (nqb-1-i, i) if the pairs fill whole rounds of
+// work-group slots to 5%.
+struct Modelled {
+    int waves = 8, paired = 0;
+    int64_t gx = 0;  // most work-groups of a sequence
+    int pieces = 1, piece_tiles = 0;
+};
+
+Modelled model_launch(int32_t batch, const int32_t *nl, int64_t heads, int64_t cus) {
+    Modelled m;
+    int64_t max_n = 0;
+    for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, nl[b]);
+    const auto pairs_of = [&](int64_t bm) {
+        int64_t n = 0;
+        for (int32_t b = 0; b < batch; ++b) n += ((nl[b] + bm - 1) / bm + 1) / 2;
+        return n * heads;
+    };
+    int64_t bm = 64, slots = cus;
+    if (pairs_of(bm) < cus) {
+        m.waves = 4;
+        bm = 32;
+        slots = 2 * cus;
+    }
+    const int64_t blocks = (max_n + bm - 1) / bm, n_pairs = pairs_of(bm);
+    const int64_t rounds = (n_pairs + slots - 1) / slots;
+    m.paired = n_pairs >= slots && rounds * slots * 20 <= n_pairs * 21;
+    m.gx = (m.paired ? (blocks + 1) / 2 : blocks) * heads;
+    return m;
+}
+
 // The key-range split of the modelled launch, in blocks of 32 positions: with
 // fewer blocks than CUs, pieces that give about two work-groups per CU; with
 // fewer than two per CU, long blocks (96 tiles and more) cut in three.
-void model_split(int32_t batch, const int32_t *nl, const int32_t *rl, int64_t heads, int64_t cus, PrefillPlan *pl) {
+void model_split(int32_t batch, const int32_t *nl, const int32_t *rl, int64_t heads, int64_t cus, Modelled *pl) {
     int max_nt = 0;
     int64_t units = 0;
     for (int32_t b = 0; b < batch; ++b) {
@@ -158,11 +191,8 @@ void model_split(int32_t batch, const int32_t *nl, const int32_t *rl, int64_t he
 }
 
 PrefillLaunch prefill_launch(int32_t batch, const int32_t *nl, const int32_t *rl, int hkv, int group, int64_t cus) {
-    PrefillPlan pl;
-    // modelled in blocks of 32 or 64 positions of up to four query heads (a
-    // group of 4 fills a block's 128 or 256 rows exactly)
     const int64_t heads = static_cast<int64_t>(hkv) * ((group + 3) / 4);
-    prefill_plan_lengths(batch, nl, static_cast<int>(heads), 4, cus, true, &pl);
+    Modelled pl = model_launch(batch, nl, heads, cus);
     if (pl.waves == 4) model_split(batch, nl, rl, heads, cus, &pl);
     const int bm = pl.waves == 4 ? 32 : 64;
     const int per_cu = pl.waves == 4 ? 2 : 1;

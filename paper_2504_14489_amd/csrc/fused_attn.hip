@@ -80,7 +80,7 @@ extern "C" mw_status mw_fused_attn(const mw_prefill_args *pre, const mw_decode_a
     DecodePlan dp;
     st = decode_prepare(dec, 0, &dp, who);  // fixed chunks: a fused work-group's barriers are uniform
     if (st != MW_OK) return st;
-    const int64_t n_pre = pp.grid_x * pp.grid_y, n_dec = (dp.units + 1) / 2;
+    const int64_t n_pre = pp.gx * pp.gy, n_dec = (dp.units + 1) / 2;
     if (n_pre + n_dec > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     st = timing_begin(timing, s);
     if (st != MW_OK) return st;
@@ -92,7 +92,7 @@ extern "C" mw_status mw_fused_attn(const mw_prefill_args *pre, const mw_decode_a
                            pool->v, pool->desc.num_pages, pp.hkv, static_cast<const uint16_t *>(pre->d_q),
                            static_cast<uint16_t *>(pre->d_out), pre->d_qo_indptr, pre->d_prefix_lens,
                            pre->d_block_table, pre->bt_stride, pp.group, pp.scale_log2, pp.batch, pp.order,
-                           static_cast<int>(pp.grid_x > 0 ? pp.grid_x : 1), n_pre, static_cast<const uint16_t *>(dec->d_q),
+                           static_cast<int>(pp.gx > 0 ? pp.gx : 1), n_pre, static_cast<const uint16_t *>(dec->d_q),
                            static_cast<uint16_t *>(dec->d_out), dec->d_seq_lens, dec->d_block_table, dec->bt_stride,
                            reinterpret_cast<float *>(ws), reinterpret_cast<float2 *>(ws + dp.off_ml),
                            reinterpret_cast<int32_t *>(ws + dp.off_meta), dec->batch, dp.group, dp.scale_log2,

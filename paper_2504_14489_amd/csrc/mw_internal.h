@@ -121,36 +121,31 @@ mw_status decode_combine_launch(const mw_decode_args *a, const DecodePlan &p, hi
 
 // Checked launch parameters of one prefill call.
 struct PrefillPlan {
-    int hkv, group, paired;
-    int waves;            // 8 (256-row query blocks) or 4 (128-row blocks)
-    int64_t gx;           // most work-groups of a sequence; 0: nothing to do
-    int batch;
-    // the launch: grid and order of the query blocks (prefill_block.h)
-    int64_t grid_x;
-    int grid_y, order;
-    int64_t blocks;       // query blocks of the batch, per kv head
+    int hkv, group, batch;
+    // the launch: waves of a work-group (8: 256-row query blocks; 4: 128-row
+    // blocks, or the halves of dual blocks), grid (gx 0: nothing to do) and order
+    // of the blocks (prefill_block.h)
+    int waves, order;
+    int64_t gx;
+    int gy;
     bool table_in_lds;    // every block-table entry a work-group needs fits its LDS copy
     float scale_log2;
-    // key-range split (4-wave blocks only; planned by prefill_split_plan)
+    // calls that may split key ranges (planned by prefill_split_plan)
+    bool dual;            // dual blocks
+    int64_t big_units;    // 256-row units of a launch whose last round runs as dual halves; 0: not such a launch
     int pieces;           // most pieces of any block; 1: no split
     int piece_tiles;      // target key tiles per piece
     int64_t rows;         // sum of the new lengths (rows of the workspace partials)
-    int body;             // a 4-wave plan's body where key ranges may be split
     size_t split_bytes;   // workspace the split needs
 };
-enum { kBodyPlain = 0, kBodyDual = 1, kBodyEight = 2 };  // as planned; dual blocks; 8-wave single blocks
 // Validates a prefill call's arguments and plans it for a stream that may use
-// `cus` CUs (block pairing and, with allow_small, the work-group size depend
-// on it).
-mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who);
-// The launch plan of a prefill call from its lengths alone (no validation):
-// waves, pairing, grid and order for a stream of `cus` CUs; used by
-// prefill_prepare and by the latency predictor, which simulates the launch.
-void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int group, int64_t cus,
-                          bool allow_small, PrefillPlan *p);
-// Plans the body and the key-range split of a 4-wave call on `cus` CUs (cus = 0:
-// the largest split any stream could take); fills body, pieces, piece_tiles,
-// rows and split_bytes.  Lengths must have been validated.
+// `cus` CUs: one launch of 8-wave blocks (with allow_small, or of 4-wave ones),
+// or with split whatever prefill_split_plan finds best.
+mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who,
+                          bool split = false);
+// Plans body, order and key-range split of a call on `cus` CUs from its lengths
+// (cus = 0: only the largest split any stream could take); hkv and group must be
+// set, lengths must have been validated.
 void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hq,
                         int64_t cus, PrefillPlan *p);
 

@@ -159,6 +159,156 @@ k_prefill_merge(const float *__restrict__ ws_o, const float2 *__restrict__ ws_ml
 // of a wave each).
 constexpr int kMaxSorted = 64;
 
+// The work-groups of one way to launch a call, from its lengths: `n` of them in
+// a grid of `grid` (the rest find no block), which run `blocks` query blocks of
+// `tiles` key tiles in all; tiles of the longest, of the lightest and of the last
+// sequence's longest.
+struct Jobs {
+    int64_t n = 0, grid = 0, blocks = 0;
+    double tiles = 0, longest = 0, lightest = 1e30, last = 0;
+};
+
+// What a work-group takes (us): around its tiles and per tile, alone on its CU
+// and on a full chip; to find its block in a batch in length order; a work-group
+// without a block; and how a launch of more work-groups than slots ends (shares
+// of the lightest one, of the last round's idle part, of how much the last
+// sequence's longest block exceeds the lightest).
+struct BodyCost {
+    double around_alone, per_alone, around, per, empty, search, end_lightest, end_round, spread, end_last, late;
+};
+// Fitted by least squares of the log error to 2061 calls (1 to 16 sequences of 1
+// to 4096 new tokens over 0 to 28672, groups of 1 to 16, 32 to 256 CUs, each
+// body, order and number of pieces measured on each: 15406 launches, 2%, 3% and
+// 5% off in the median). The cheapest by these is 2% slower than the fastest
+// measured of each call (geometric mean, calls of 8 us and more); with the choice
+// by CU count and an earlier fit it was 7%, and 88 calls instead of 41 were more
+// than 2% slower than with the four-heads-a-block layout.
+constexpr BodyCost kCost4{4.4, 1.18, 4.5, 1.57, 0.8, 0.9, 0.19, 0.36, 0.0, 0.22, 1.0};    // 2 work-groups per CU
+constexpr BodyCost kCost8{6.1, 1.27, 4.7, 1.48, 3.7, 1.3, 0.04, 0.67, 0.03, 0.23, 2.5};
+constexpr BodyCost kCostDual{5.7, 0.69, 5.3, 0.845, 0.8, 1.15, 0.28, 0.60, 0.53, 0.10, 1.1};
+constexpr double kMergeUs = 5.5, kMergeBytesPerUs = 8.8e6;  // the second launch, and its partials' way out and back
+
+// Time of a launch (us, without what is common to all), for CUs that hold
+// per_cu work-groups each.
+double launch_us(const BodyCost &c, const Jobs &j, int64_t cus, int per_cu, bool sorted, bool one_sequence) {
+    if (j.n == 0) return 0.0;
+    const int64_t slots = per_cu * cus;
+    const double search = sorted ? c.search : 0.0;
+    const double empty = sorted ? 0.0 : c.empty * (j.grid - j.n) / slots;
+    // the longest work-group, alone on its CU or beside the heaviest of those
+    // that no longer find an empty CU
+    double us = c.around_alone * j.blocks / j.n + search + c.per_alone * j.longest;
+    if (j.n > cus) {
+        if (per_cu == 2) {
+            const double beside = std::max(j.lightest, j.longest - (j.longest - j.lightest) * cus / j.n);
+            us = std::max(us, c.around + search + c.per * beside + c.per_alone * (j.longest - beside));
+        }
+        // the even share, and past one round what the last one leaves idle
+        double share = (c.around * j.blocks + search * j.n + c.per * j.tiles) / slots + empty;
+        if (j.n > slots) {
+            const double rounds = static_cast<double>(j.n) / slots;
+            share += c.end_lightest * (c.around + c.per * j.lightest) +
+                     c.end_round * (1.0 - c.spread * (j.longest - j.lightest) / j.longest) *
+                         (std::ceil(rounds) - rounds) * (c.around * j.blocks + c.per * j.tiles) / j.n;
+            if (!sorted && !one_sequence) share += c.end_last * (c.around + c.per * (j.last - j.lightest));
+        }
+        us = std::max(us, share);
+    } else {
+        us += empty;
+    }
+    return us + (!sorted && j.grid > j.n && j.grid > slots ? c.late : 0.0);
+}
+
+// A call's work-groups on blocks of 256 rows, one each (one8) and two each, nqb-1-i
+// and i (two8), and on blocks of 128 rows (one4); most8, most4: blocks of the
+// sequence with the most.
+struct CallJobs {
+    Jobs one8, two8, one4;
+    int64_t most8 = 0, most4 = 0;
+};
+
+CallJobs count_jobs(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hkv, int group) {
+    CallJobs c;
+    const auto add = [](Jobs *j, int64_t n, double tiles, double longest, double lightest) {
+        j->n += n;
+        j->tiles += tiles;
+        j->longest = std::max(j->longest, longest);
+        j->lightest = std::min(j->lightest, lightest);
+        j->last = longest;
+    };
+    for (int32_t b = 0; b < batch; ++b) {
+        const int64_t n = h_new_lens[b], r = h_prefix_lens[b];
+        if (n == 0) continue;
+        const double last = static_cast<double>((r + n + 63) / 64);
+        const int64_t n8 = (n * group + 255) / 256, n4 = (n * group + 127) / 128;
+        const double first8 = prefill_block_tiles<int64_t>(r, n, 0, 256, group);
+        const double first4 = prefill_block_tiles<int64_t>(r, n, 0, 128, group);
+        const double pair = n8 > 1 ? first8 + last : last;
+        add(&c.one8, n8 * hkv, n8 * hkv * (first8 + last) / 2, last, first8);
+        add(&c.two8, (n8 + 1) / 2 * hkv, n8 * hkv * (first8 + last) / 2, pair, n8 % 2 == 0 ? pair : (first8 + last) / 2);
+        add(&c.one4, n4 * hkv, n4 * hkv * (first4 + last) / 2, last, first4);
+        c.most8 = std::max(c.most8, n8);
+        c.most4 = std::max(c.most4, n4);
+    }
+    c.one8.blocks = c.two8.blocks = c.one8.n;
+    c.one4.blocks = c.one4.n;
+    c.one8.grid = c.most8 * hkv * batch;
+    c.two8.grid = (c.most8 + 1) / 2 * hkv * batch;
+    c.one4.grid = c.most4 * hkv * batch;
+    return c;
+}
+
+void set_launch(PrefillPlan *p, int waves, int order, const CallJobs &c) {
+    const Jobs &j = waves == 8 ? c.one8 : c.one4;
+    const int64_t most = waves == 8 ? c.most8 : c.most4;
+    p->waves = waves;
+    p->order = order;
+    p->gx = order == kSorted ? j.n : (order == kPairs ? (most + 1) / 2 : most) * p->hkv;
+    p->gy = order == kSorted ? 1 : p->batch;
+}
+
+bool sortable(int32_t batch) { return batch > 1 && batch <= kMaxSorted; }
+
+// Plans a call as one launch of 8- or, if allowed, 4-wave blocks, the cheapest of
+// their orders; returns its time.
+double choose_plain(const CallJobs &c, int64_t cus, bool allow_small, PrefillPlan *p) {
+    double best = INFINITY;
+    const auto take = [&](double us, int waves, int order) {
+        if (us >= best) return;
+        best = us;
+        set_launch(p, waves, order, c);
+    };
+    const bool one = p->batch == 1;
+    take(launch_us(kCost8, c.one8, cus, 1, false, one), 8, kPerSequence);
+    take(launch_us(kCost8, c.two8, cus, 1, false, one), 8, kPairs);
+    if (sortable(p->batch)) take(launch_us(kCost8, c.one8, cus, 1, true, one), 8, kSorted);
+    if (!allow_small) return best;
+    take(launch_us(kCost4, c.one4, cus, 2, false, one), 4, kPerSequence);
+    if (sortable(p->batch)) take(launch_us(kCost4, c.one4, cus, 2, true, one), 4, kSorted);
+    return best;
+}
+
+// Units (block, kv head) that a call of 256-row blocks on `cus` CUs runs as such
+// when the rest, its last and partial round, goes to dual blocks; 0: not such a
+// call.  Blocks taken longest first fill CUs evenly when they differ much in
+// length (a prompt without a prefix), so only calls whose lightest block has at
+// least half the tiles of the heaviest are treated.  There the last round costs a
+// whole block's time for any fraction f of a round; as dual blocks it costs a
+// little over half a block's while f <= 1/2.  Simulated over 2.3 to 5.3 rounds the
+// launch gets 5-17% shorter, and past f = 1/2 longer.  Measured: the 70B layer's
+// 2048-token chunk over 6144 cached tokens on 96 CUs (5.33 rounds) next to its
+// decode, 958 -> 911 us a step.
+int64_t big_units(const CallJobs &c, int64_t cus, const PrefillPlan &p) {
+    const int64_t units = c.one8.n, whole = units / cus * cus;
+    if (whole < 2 * cus || whole == units || 2 * (units - whole) > cus) return 0;
+    if (2 * c.one8.lightest < c.one8.longest) return 0;
+    // more than one sequence: in length order, where that pays by itself
+    if (p.batch > 1 && (!sortable(p.batch) || launch_us(kCost8, c.one8, cus, 1, true, false) >
+                                                  launch_us(kCost8, c.one8, cus, 1, false, false)))
+        return 0;
+    return whole / p.hkv * p.hkv;
+}
+
 }  // namespace
 
 namespace mw {
@@ -169,27 +319,17 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     p->piece_tiles = 0;
     p->split_bytes = 0;
     p->rows = 0;
-    p->body = kBodyPlain;
-    int max_nt = 0, min_nt = INT32_MAX;
-    int64_t units = 0, tiles = 0, units8 = 0, tiles8 = 0;  // 128- and 256-row query blocks x kv heads, their key tiles
-    for (int32_t b = 0; b < batch; ++b) {
-        const int n = h_new_lens[b], r = h_prefix_lens[b];
-        p->rows += n;
-        const int64_t blocks = (static_cast<int64_t>(n) * p->group + 127) / 128, blocks8 = (blocks + 1) / 2;
-        if (blocks == 0) continue;
-        const int first = prefill_block_tiles<int64_t>(r, n, 0, 128, p->group), last = static_cast<int>((static_cast<int64_t>(r) + n + 63) / 64);
-        max_nt = std::max(max_nt, last);
-        min_nt = std::min(min_nt, first);
-        units += blocks;
-        tiles += blocks * (first + last) / 2;
-        units8 += blocks8;
-        tiles8 += blocks8 * (prefill_block_tiles<int64_t>(r, n, 0, 256, p->group) + last) / 2;
+    p->big_units = 0;
+    p->dual = false;
+    p->batch = batch;
+    for (int32_t b = 0; b < batch; ++b) p->rows += h_new_lens[b];
+    const CallJobs c = count_jobs(batch, h_new_lens, h_prefix_lens, p->hkv, p->group);
+    const Jobs &j = c.one4;
+    if (j.n == 0) {
+        set_launch(p, 8, kPerSequence, c);
+        return;
     }
-    units *= p->hkv;
-    tiles *= p->hkv;
-    units8 *= p->hkv;
-    tiles8 *= p->hkv;
-    if (p->waves != 4 || units == 0) return;
+    const int max_nt = static_cast<int>(j.longest), min_nt = static_cast<int>(j.lightest);
     const auto bytes_for = [&](int pieces) {
         return pieces > 1 ? static_cast<size_t>(pieces) * p->rows * hq * (kHeadDim * 4 + 8) : 0;
     };
@@ -199,95 +339,52 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
         p->split_bytes = bytes_for(p->pieces);
         return;
     }
-    // The cheapest body, and for dual blocks number of pieces of the longest
-    // block, by their time in microseconds, fitted to 40 calls of 1 to 16
-    // sequences, 1 to 4096 new tokens over 0 to 8000, groups of 1 to 8, on 96
-    // to 256 CUs (each body and 1, 2 and 4 pieces measured on each; the choice
-    // is within 8% of the best measured on all of them).  The fit dates from
-    // before the 128-row bodies took Q through LDS, which made both alike 0.5
-    // to 1.1 us faster.  A work-group takes `around` and `per` for each key
-    // tile.  With no more work-groups than slots the call lasts as long as its
-    // longest one; past that as the even share of the work and half the
-    // lightest one, dispatched last.
-    struct Cost {
-        double around, per;
-    };
-    const Cost kAlone4{5.1, units <= cus ? 1.2 : 1.35}, kShared4{5.1, 2.0}, kDual{6.8, 0.75}, kFullDual{7.0, 0.79},
-        kAlone8{6.5, 1.45}, kFull8{7.0, 1.6};
-    const auto time_of = [&](int64_t n, double n_tiles, double longest, double lightest, int64_t slots, Cost alone,
-                             Cost full) {
-        const double one = alone.around + alone.per * longest;
-        if (n <= cus) return one;
-        return std::max(one, (full.around * n + full.per * n_tiles) / slots +
-                                 0.5 * (full.around + full.per * lightest) * (n > slots));
-    };
-    const double us4 = time_of(units, tiles, max_nt, min_nt, 2 * cus, kAlone4, kShared4);
-    const double us8 = time_of(units8, tiles8, max_nt, min_nt, cus, kAlone8, kFull8);
-    // Pieces: partials are written and read at about 4 TB/s for the rows of
-    // blocks longer than a piece, in a second launch (2 us).  Two blocks per CU
-    // and more even out by themselves and are never cut; fewer, of 96 tiles and
-    // more, always.
-    const bool must_cut = units < 2 * cus && max_nt >= 96;
-    double best = INFINITY;
-    int best_pt = 0;
-    for (int k = must_cut ? 2 : 1; k <= (units < 2 * cus ? kPrefillMaxPieces : 1); ++k) {
-        const int pt = std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k);
-        if (k > 1 && pt >= max_nt) break;
-        const double cut = k == 1 ? 0.0 : std::min(1.0, static_cast<double>(max_nt - pt) / (max_nt - min_nt + 1));
-        double us = time_of(units * k, tiles, pt, k == 1 ? min_nt : 0.5 * pt, cus, kDual, kFullDual);
-        if (k > 1) us += 2.0 + cut * 2.0 * bytes_for(k) / 4e6;
-        if (us < best) {
-            best = us;
-            best_pt = k > 1 ? pt : 0;
-        }
-    }
-    if (!must_cut && us8 < std::min(best, us4)) {
-        p->body = kBodyEight;
+    p->big_units = big_units(c, cus, *p);
+    if (p->big_units > 0) {
+        set_launch(p, 8, batch == 1 ? kPerSequence : kSorted, c);
         return;
     }
-    if (!must_cut && us4 < best) return;
-    p->body = kBodyDual;
-    if (best_pt == 0) return;
-    p->piece_tiles = best_pt;
-    p->pieces = prefill_pieces(max_nt, best_pt, kPrefillMaxPieces);
+    const double plain = choose_plain(c, cus, true, p);
+    // Dual blocks, whole or in pieces.  Only launches of few blocks are cut: two
+    // blocks per CU and more even out by themselves.  Two kinds always are, as
+    // every caller's workspace provides for: fewer than two blocks per CU of 96
+    // tiles and more, and blocks of 10 tiles and more of which four pieces each
+    // fit the CUs at once (whole ones are up to 2 us faster at 10 to 13 tiles, and
+    // 1 to 5 us slower from 15).
+    const bool cuttable = c.two8.n < cus && j.n < 2 * cus;
+    const bool must_cut = cuttable && (max_nt >= 96 || (4 * j.n <= cus && max_nt >= 10));
+    double best = must_cut ? INFINITY : plain;
+    for (int k = must_cut ? 2 : 1; k <= (cuttable ? kPrefillMaxPieces : 1); ++k) {
+        const int pt = std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k);
+        if (k > 1 && pt >= max_nt) break;
+        Jobs jk = j;
+        double merge = 0.0;
+        if (k > 1) {
+            jk.n *= k;
+            jk.grid *= k;
+            jk.blocks *= k;
+            jk.longest = pt;
+            jk.lightest = 0.5 * pt;
+            jk.last = std::min(jk.last, jk.longest);
+            const double cut = std::min(1.0, static_cast<double>(max_nt - pt) / (max_nt - min_nt + 1));
+            merge = kMergeUs + cut * 2.0 * bytes_for(k) / kMergeBytesPerUs;
+        }
+        for (int sorted = 0; sorted <= (sortable(batch) ? 1 : 0); ++sorted) {
+            const double us = launch_us(kCostDual, jk, cus, 1, sorted != 0, batch == 1) + merge;
+            if (us >= best) continue;
+            best = us;
+            p->dual = true;
+            p->piece_tiles = k > 1 ? pt : 0;
+            set_launch(p, 4, sorted ? kSorted : kPerSequence, c);
+        }
+    }
+    if (!p->dual || p->piece_tiles == 0) return;
+    p->pieces = prefill_pieces(max_nt, p->piece_tiles, kPrefillMaxPieces);
     p->split_bytes = bytes_for(p->pieces);
 }
 
-// Units (block, kv head) that a call of 256-row blocks on `cus` CUs runs as such
-// when the rest, its last and partial round, goes to dual blocks; 0: all of
-// them, one launch of k_prefill_attn.  Blocks taken longest first fill CUs
-// evenly when they differ much in length (a prompt without a prefix), so only
-// calls whose lightest block has at least half the tiles of the heaviest are
-// treated.  There the last round costs a whole block's time for any fraction f
-// of a round; as dual blocks it costs a little over half a block's while
-// f <= 1/2.  Simulated over 2.3 to 5.3 rounds the launch gets 5-17% shorter,
-// and past f = 1/2 longer.  Measured: the 70B layer's 2048-token chunk over 6144
-// cached tokens on 96 CUs (5.33 rounds) next to its decode, 958 -> 911 us a
-// step.
-static int64_t prefill_big_units(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int64_t cus,
-                                 const PrefillPlan &p) {
-    if (p.waves != 8 || p.grid_y != 1 || p.order == kPairs) return 0;
-    const int64_t units = p.blocks * p.hkv, whole = units / cus * cus;
-    if (whole < 2 * cus || whole == units || 2 * (units - whole) > cus) return 0;
-    int most = 0, least = INT32_MAX;
-    for (int32_t b = 0; b < batch; ++b) {
-        if (h_new_lens[b] == 0) continue;
-        most = std::max(most, static_cast<int>((static_cast<int64_t>(h_prefix_lens[b]) + h_new_lens[b] + 63) / 64));
-        least = std::min(least, prefill_block_tiles<int64_t>(h_prefix_lens[b], h_new_lens[b], 0, 256, p.group));
-    }
-    if (2 * least < most) return 0;
-    return whole / p.hkv * p.hkv;
-}
-
-// Pairs of query blocks of `block_rows` rows over a batch's sequences.
-static int64_t prefill_pairs(int32_t batch, const int32_t *h_new_lens, int group, int64_t block_rows) {
-    int64_t n_pairs = 0;
-    for (int32_t b = 0; b < batch; ++b)
-        n_pairs += ((static_cast<int64_t>(h_new_lens[b]) * group + block_rows - 1) / block_rows + 1) / 2;
-    return n_pairs;
-}
-
-mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who) {
+mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who,
+                          bool split) {
     if (!a || !a->pool || a->batch < 0 || a->batch > 65535 || a->bt_stride < 1 ||
         (a->batch > 0 && (!a->h_new_lens || !a->h_prefix_lens)))
         return fail(MW_ERR_INVALID_ARG, "%s: bad arguments", who);
@@ -314,81 +411,19 @@ mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_smal
         return fail(MW_ERR_INVALID_ARG, "%s: NULL device pointer", who);
     if (max_n > 0 && (!aligned16(a->d_q) || !aligned16(a->d_out)))
         return fail(MW_ERR_INVALID_ARG, "%s: Q and O must be 16-byte aligned", who);
-    prefill_plan_lengths(a->batch, a->h_new_lens, shape->num_kv_heads, shape->num_q_heads / shape->num_kv_heads, cus,
-                         allow_small, p);
+    *p = PrefillPlan{};
+    p->hkv = shape->num_kv_heads;
+    p->group = shape->num_q_heads / shape->num_kv_heads;
+    p->batch = a->batch;
+    p->pieces = 1;
     p->table_in_lds = max_pages <= kBtCache;
     p->scale_log2 = shape->scale * kLog2e;
-    // Ordering over the batch costs a work-group 1.3 us to find its block: worth
-    // it when blocks are long against the rounds of work-groups (an eighth of
-    // the longest one's time), not for a launch that is resident at once.
-    if (p->order == kSorted) {
-        int64_t max_n_rows = 0, longest = 0;
-        for (int32_t b = 0; b < a->batch; ++b) {
-            max_n_rows = std::max<int64_t>(max_n_rows, static_cast<int64_t>(a->h_new_lens[b]) * p->group);
-            if (a->h_new_lens[b] > 0)
-                longest = std::max<int64_t>(longest, (static_cast<int64_t>(a->h_prefix_lens[b]) + a->h_new_lens[b] + 63) / 64);
-        }
-        const int64_t rows = 32 * p->waves, slots = p->waves == 8 ? cus : 2 * cus;
-        const int64_t grid = (max_n_rows + rows - 1) / rows * p->hkv * a->batch;
-        if (grid <= slots || 1.6 * longest * slots < 8 * 1.3 * grid) {
-            p->order = p->paired ? kPairs : kPerSequence;
-            p->grid_x = p->gx;
-            p->grid_y = a->batch;
-        }
-    }
-    if (p->grid_x > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
+    if (split)
+        prefill_split_plan(a->batch, a->h_new_lens, a->h_prefix_lens, shape->num_q_heads, cus, p);
+    else
+        choose_plain(count_jobs(a->batch, a->h_new_lens, a->h_prefix_lens, p->hkv, p->group), cus, allow_small, p);
+    if (p->gx * p->pieces > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     return MW_OK;
-}
-
-void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int group, int64_t cus,
-                          bool allow_small, PrefillPlan *p) {
-    p->hkv = hkv;
-    p->group = group;
-    p->batch = batch;
-    p->table_in_lds = true;
-    p->scale_log2 = 0.f;
-    p->paired = 0;
-    p->gx = p->grid_x = p->blocks = 0;
-    p->grid_y = 1;
-    p->order = kPerSequence;
-    p->pieces = 1;
-    p->piece_tiles = 0;
-    p->rows = 0;
-    p->split_bytes = 0;
-    p->waves = 8;
-    int64_t max_n = 0;
-    for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, h_new_lens[b]);
-    if (max_n == 0) return;
-    auto pairs_of = [&](int64_t rows) { return prefill_pairs(batch, h_new_lens, group, rows) * hkv; };
-    // Eight waves (256-row blocks, one work-group per CU) unless their pairs
-    // would not even give every CU one: then four waves (128-row blocks,
-    // two work-groups per CU), which doubles the work-groups.
-    int64_t rows = 256, slots = cus;
-    if (allow_small && pairs_of(rows) < cus) {
-        p->waves = 4;
-        rows = 128;
-        slots = 2 * cus;
-    }
-    // Pair blocks only when the pairs fill whole rounds of the work-group slots
-    // of the stream's CUs: equal-cost pairs then finish together.  Otherwise
-    // single blocks, heaviest first, fill the last round better.
-    const int64_t max_blocks = (max_n * group + rows - 1) / rows;
-    const int64_t n_pairs = pairs_of(rows);
-    const int64_t rounds = (n_pairs + slots - 1) / slots;
-    p->paired = n_pairs >= slots && rounds * slots * 20 <= n_pairs * 21;
-    p->gx = (p->paired ? (max_blocks + 1) / 2 : max_blocks) * hkv;
-    for (int32_t b = 0; b < batch; ++b) p->blocks += (static_cast<int64_t>(h_new_lens[b]) * group + rows - 1) / rows;
-    // Up to 64 sequences: blocks ordered over the whole batch (a sequence at a
-    // time leaves the last one's long blocks to the end of the launch, and
-    // gives every sequence as many work-groups as the longest needs)
-    if (batch > 1 && batch <= kMaxSorted) {
-        p->order = kSorted;
-        p->grid_x = p->blocks * hkv;
-    } else {
-        p->order = p->paired ? kPairs : kPerSequence;
-        p->grid_x = p->gx;
-        p->grid_y = batch;
-    }
 }
 
 }  // namespace mw
@@ -397,10 +432,10 @@ void prefill_plan_lengths(int32_t batch, const int32_t *h_new_lens, int hkv, int
 static mw_status launch_plain(const mw_prefill_args &a, const PrefillPlan &pl, hipStream_t s, mw_timing *timing) {
     mw_status st = timing_begin(timing, s);
     if (st != MW_OK) return st;
-    if (pl.grid_x > 0) {
+    if (pl.gx > 0) {
         auto kernel = pl.waves == 4 ? (pl.table_in_lds ? k_prefill_attn<true, 4> : k_prefill_attn<false, 4>)
                                     : (pl.table_in_lds ? k_prefill_attn<true, 8> : k_prefill_attn<false, 8>);
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.grid_x), pl.grid_y), dim3(64 * pl.waves), 0, s,
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.gx), pl.gy), dim3(64 * pl.waves), 0, s,
                            a.pool->k, a.pool->v, static_cast<const uint16_t *>(a.d_q),
                            static_cast<uint16_t *>(a.d_out), a.d_qo_indptr, a.d_prefix_lens, a.d_block_table,
                            a.bt_stride, a.batch, pl.hkv, pl.group, a.pool->desc.num_pages, pl.scale_log2, pl.order);
@@ -443,9 +478,6 @@ extern "C" mw_status mw_prefill_workspace_size(const mw_attn_shape *shape, int32
     PrefillPlan pl{};
     pl.hkv = shape->num_kv_heads;
     pl.group = shape->num_q_heads / pl.hkv;
-    // the split runs where the launch takes 4-wave blocks (as in prefill_prepare);
-    // without a CU count, size for any stream
-    pl.waves = num_cus == 0 || prefill_pairs(batch, h_new_lens, pl.group, 256) * pl.hkv < num_cus ? 4 : 8;
     prefill_split_plan(batch, h_new_lens, h_prefix_lens, shape->num_q_heads, num_cus, &pl);
     *bytes = pl.split_bytes;
     return MW_OK;
@@ -464,13 +496,10 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
     hipStream_t s = static_cast<hipStream_t>(stream);
     PrefillPlan pl;
     const int64_t cus = stream_cus(s);
-    mw_status st = prefill_prepare(&a, cus, true, &pl, who);
+    mw_status st = prefill_prepare(&a, cus, true, &pl, who, true);
     if (st != MW_OK) return st;
-    const int64_t n_big = prefill_big_units(batch, h_new_lens, h_prefix_lens, cus, pl);
-    if ((pl.waves == 8 && n_big == 0) || pl.gx == 0)
-        return launch_plain(a, pl, s, timing);
-    if (n_big > 0) {
-        const int64_t units = pl.blocks * pl.hkv;
+    if (pl.big_units > 0) {
+        const int64_t n_big = pl.big_units, units = pl.gx;
         st = timing_begin(timing, s);
         if (st != MW_OK) return st;
         auto kernel = pl.table_in_lds ? k_prefill_mixed<true> : k_prefill_mixed<false>;
@@ -484,24 +513,13 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
         timing_end(timing);
         return st;
     }
-    prefill_split_plan(batch, h_new_lens, h_prefix_lens, shape->num_q_heads, cus, &pl);
-    if (pl.body != kBodyDual) {
-        if (pl.body == kBodyEight) {
-            st = prefill_prepare(&a, cus, false, &pl, who);
-            if (st != MW_OK) return st;
-        }
-        return launch_plain(a, pl, s, timing);
-    }
+    if (!pl.dual) return launch_plain(a, pl, s, timing);
     const bool cut = pl.pieces > 1;
     if (cut && (!d_workspace || !aligned16(d_workspace) || workspace_bytes < pl.split_bytes))
         return fail(MW_ERR_INVALID_ARG, "%s: the split needs a 16-byte aligned workspace of %zu bytes (got %zu)",
                     who, pl.split_bytes, workspace_bytes);
     int64_t max_n = 0;
     for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, h_new_lens[b]);
-    // single blocks, over the whole batch or a sequence at a time
-    const int64_t gx = (pl.order == kSorted ? pl.blocks : (max_n * pl.group + 127) / 128) * pl.hkv;
-    const int order = pl.order == kSorted ? kSorted : kPerSequence;
-    if (gx * pl.pieces > 0x7fffffff) return fail(MW_ERR_UNSUPPORTED, "%s: grid too large", who);
     st = timing_begin(timing, s);
     if (st != MW_OK) return st;
     float *ws_o = static_cast<float *>(d_workspace);
@@ -510,10 +528,10 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
                                                    kHeadDim * 4);
     auto kernel = cut ? (pl.table_in_lds ? k_prefill_dual<true, true> : k_prefill_dual<false, true>)
                       : (pl.table_in_lds ? k_prefill_dual<true, false> : k_prefill_dual<false, false>);
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gx * pl.pieces), pl.grid_y), dim3(512), 0, s, pool->k,
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.gx * pl.pieces), pl.gy), dim3(512), 0, s, pool->k,
                        pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out), d_qo_indptr,
                        d_prefix_lens, d_block_table, bt_stride, batch, pl.hkv, pl.group, pool->desc.num_pages,
-                       pl.scale_log2, order, ws_o, ws_ml, pl.rows, pl.piece_tiles, pl.pieces);
+                       pl.scale_log2, pl.order, ws_o, ws_ml, pl.rows, pl.piece_tiles, pl.pieces);
     st = check_launch("k_prefill_dual");
     if (st != MW_OK) return st;
     st = timing_kernel_done(timing, s);
