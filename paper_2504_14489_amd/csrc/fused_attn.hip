@@ -31,10 +31,10 @@ static_assert(kDecodeHalf % 16 == 0, "decode LDS halves stay 16-byte aligned");
 
 template <bool kTableInLds>
 __global__ void __launch_bounds__(kThreadsFused, 1)
-k_fused_attn(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool, int num_pages, int hkv,
+k_fused_attn(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool, int num_pages, pf::Divisor hkv,
              // prefill
              const uint16_t *__restrict__ pq, uint16_t *__restrict__ pout, const int32_t *__restrict__ qo_indptr,
-             const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ pbt, int pbt_stride, int pgroup,
+             const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ pbt, int pbt_stride, pf::Divisor pgroup,
              float pscale_log2, int pbatch, int order, int gx, int64_t n_pre,
              // decode
              const uint16_t *__restrict__ dq, uint16_t *__restrict__ dout, const int32_t *__restrict__ seq_lens,
@@ -89,9 +89,9 @@ extern "C" mw_status mw_fused_attn(const mw_prefill_args *pre, const mw_decode_a
         char *ws = static_cast<char *>(dec->d_workspace);
         auto kernel = pp.table_in_lds ? k_fused_attn<true> : k_fused_attn<false>;
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_pre + n_dec)), dim3(kThreadsFused), 0, s, pool->k,
-                           pool->v, pool->desc.num_pages, pp.hkv, static_cast<const uint16_t *>(pre->d_q),
+                           pool->v, pool->desc.num_pages, pf::Divisor(pp.hkv), static_cast<const uint16_t *>(pre->d_q),
                            static_cast<uint16_t *>(pre->d_out), pre->d_qo_indptr, pre->d_prefix_lens,
-                           pre->d_block_table, pre->bt_stride, pp.group, pp.scale_log2, pp.batch, pp.order,
+                           pre->d_block_table, pre->bt_stride, pf::Divisor(pp.group), pp.scale_log2, pp.batch, pp.order,
                            static_cast<int>(pp.gx > 0 ? pp.gx : 1), n_pre, static_cast<const uint16_t *>(dec->d_q),
                            static_cast<uint16_t *>(dec->d_out), dec->d_seq_lens, dec->d_block_table, dec->bt_stride,
                            reinterpret_cast<float *>(ws), reinterpret_cast<float2 *>(ws + dp.off_ml),

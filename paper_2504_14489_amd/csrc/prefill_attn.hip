@@ -16,7 +16,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1)
 k_prefill_attn(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
                const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
                const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
-               const int32_t *__restrict__ bt, int bt_stride, int batch, int hkv, int group, int num_pages,
+               const int32_t *__restrict__ bt, int bt_stride, int batch, Divisor hkv, Divisor group, int num_pages,
                float scale_log2, int order) {
     __shared__ __attribute__((aligned(1024))) uint16_t s_k[2 * TILE];
     __shared__ __attribute__((aligned(1024))) uint16_t s_v[2 * TILE];
@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(512, 1)
 k_prefill_dual(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
                const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
                const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
-               const int32_t *__restrict__ bt, int bt_stride, int batch, int hkv, int group, int num_pages,
+               const int32_t *__restrict__ bt, int bt_stride, int batch, Divisor hkv, Divisor group, int num_pages,
                float scale_log2, int order, float *__restrict__ ws_o, float2 *__restrict__ ws_ml,
                int64_t rows, int piece_tiles, int max_pieces) {
     __shared__ __attribute__((aligned(1024))) uint16_t s_k[4 * TILE];
@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(512, 1)
 k_prefill_mixed(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
                 const uint16_t *__restrict__ q, uint16_t *__restrict__ out,
                 const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
-                const int32_t *__restrict__ bt, int bt_stride, int batch, int hkv, int group, int num_pages,
+                const int32_t *__restrict__ bt, int bt_stride, int batch, Divisor hkv, Divisor group, int num_pages,
                 float scale_log2, int order, int n_big) {
 #ifdef __HIP_DEVICE_COMPILE__  // the host pass refuses a second use of one prefill_block instantiation
     __shared__ __attribute__((aligned(1024))) uint16_t s_k[4 * TILE];
@@ -71,8 +71,8 @@ k_prefill_mixed(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__
     // past n_big, kv heads fastest, then the unit's two halves
     const int x = blockIdx.x, over = x - n_big;
     const bool big = over < 0;
-    const int half = big ? 0 : over / hkv % 2;
-    const int unit = big ? x : n_big + over / (2 * hkv) * hkv + over % hkv;
+    const int row = big ? 0 : over / hkv, half = row & 1;
+    const int unit = big ? x : n_big + over - (row + 1) / 2 * hkv;
     Item item;
     if (!work_item<256>(qo_indptr, prefix_lens, batch, hkv, group, order, unit, 0, item)) return;
     if (big) {
@@ -438,7 +438,7 @@ static mw_status launch_plain(const mw_prefill_args &a, const PrefillPlan &pl, h
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.gx), pl.gy), dim3(64 * pl.waves), 0, s,
                            a.pool->k, a.pool->v, static_cast<const uint16_t *>(a.d_q),
                            static_cast<uint16_t *>(a.d_out), a.d_qo_indptr, a.d_prefix_lens, a.d_block_table,
-                           a.bt_stride, a.batch, pl.hkv, pl.group, a.pool->desc.num_pages, pl.scale_log2, pl.order);
+                           a.bt_stride, a.batch, Divisor(pl.hkv), Divisor(pl.group), a.pool->desc.num_pages, pl.scale_log2, pl.order);
         st = check_launch("k_prefill_attn");
         if (st != MW_OK) return st;
     }
@@ -505,7 +505,7 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
         auto kernel = pl.table_in_lds ? k_prefill_mixed<true> : k_prefill_mixed<false>;
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_big + 2 * (units - n_big))), dim3(512), 0, s, pool->k,
                            pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out), d_qo_indptr,
-                           d_prefix_lens, d_block_table, bt_stride, batch, pl.hkv, pl.group, pool->desc.num_pages,
+                           d_prefix_lens, d_block_table, bt_stride, batch, Divisor(pl.hkv), Divisor(pl.group), pool->desc.num_pages,
                            pl.scale_log2, pl.order, static_cast<int>(n_big));
         st = check_launch("k_prefill_mixed");
         if (st != MW_OK) return st;
@@ -530,7 +530,7 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
                       : (pl.table_in_lds ? k_prefill_dual<true, false> : k_prefill_dual<false, false>);
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pl.gx * pl.pieces), pl.gy), dim3(512), 0, s, pool->k,
                        pool->v, static_cast<const uint16_t *>(d_q), static_cast<uint16_t *>(d_out), d_qo_indptr,
-                       d_prefix_lens, d_block_table, bt_stride, batch, pl.hkv, pl.group, pool->desc.num_pages,
+                       d_prefix_lens, d_block_table, bt_stride, batch, Divisor(pl.hkv), Divisor(pl.group), pool->desc.num_pages,
                        pl.scale_log2, pl.order, ws_o, ws_ml, pl.rows, pl.piece_tiles, pl.pieces);
     st = check_launch("k_prefill_dual");
     if (st != MW_OK) return st;

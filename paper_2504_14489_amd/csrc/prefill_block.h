@@ -171,7 +171,7 @@ enum { kPerSequence = 0, kPairs = 1, kSorted = 2 };
 // kBR: query rows per block.  Uniform over the work-group.
 template <int kBR>
 __device__ __forceinline__ bool work_item(const int32_t *__restrict__ qo_indptr,
-                                          const int32_t *__restrict__ prefix_lens, int batch, int hkv, int group,
+                                          const int32_t *__restrict__ prefix_lens, int batch, Divisor hkv, Divisor group,
                                           int order, int x, int y, Item &it) {
     int j = x / hkv;
     it.kvh = x - j * hkv;
@@ -240,7 +240,7 @@ template <bool kTableInLds, int NW, bool kDual = false, bool kSplit = false>
 __device__ __forceinline__ void
 prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool,
               const uint16_t *__restrict__ q, uint16_t *__restrict__ out, const int32_t *__restrict__ bt,
-              int bt_stride, int hkv, int group, int num_pages, float scale_log2,
+              int bt_stride, Divisor hkv, Divisor group, int num_pages, float scale_log2,
               // the block(s) to run, and the LDS buffers: K and V tiles
               // (2 * TILE each, or 4 * TILE with kDual, 1024-byte aligned) and
               // the block-table copy (kBtCache entries)
@@ -777,6 +777,9 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
                 if (grp == 1) vm_wait();
                 wg_barrier();
                 for (; __builtin_expect(t + 1 < nt_w, 1); ++t) {
+                    // (a 64-byte line: where other code moved the head off it, the 70B
+                    // layer's chunk on 96 CUs took 860 us instead of 837)
+                    asm volatile(".p2align 6");
                     if (grp == 1) period_loads(t + 1);
                     softmax_phase(t, [](int) {});
                     wg_barrier();
@@ -937,6 +940,7 @@ prefill_block(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ v
         // writes 16 bytes per lane and four whole 256-byte rows per
         // instruction.  Row q of the staged tile holds its 16-byte chunk c at
         // chunk c ^ (q % 16).
+        if (nt_w == 0) continue;  // (of no rows)
         const float lt = l_run + __shfl_xor(l_run, 32);
         const float inv = 1.f / lt;
         char *st = reinterpret_cast<char *>((wave < 4 ? s_k : s_v) + (wave & 3) * (32 * ROW));

@@ -61,14 +61,12 @@ __host__ __device__ __forceinline__ void dual_schedule(int grp, int total, int m
             MW_STEP(kDualMatrix, u);
             MW_STEP(kDualBarrier, u);
         }
-        if (mine == own) {
-            MW_STEP(kDualLastSoftmax, u);
-            MW_STEP(kDualWaitAll, u);
-        } else {
-            MW_STEP(kDualLoadK, u);
-            MW_STEP(kDualLastSoftmax, u);
+        if (mine < own) MW_STEP(kDualLoadK, u);
+        MW_STEP(kDualLastSoftmax, u);
+        if (mine < own)
             MW_STEP(kDualWaitOlder, u);
-        }
+        else
+            MW_STEP(kDualWaitAll, u);
         MW_STEP(kDualBarrier, u);
         MW_STEP(kDualLastMatrix, u);
         if (mine < own) MW_STEP(kDualLoadV, u);

@@ -141,6 +141,21 @@ void prefill_sizes() {
     }
 }
 
+// Quotients by a divisor with a precomputed reciprocal: every divisor up to 4096 and
+// random ones, at multiples, next to them and at the ends of the range.
+void divisors() {
+    for (int it = 0; it < 6000; ++it) {
+        const int d = it < 4096 ? it + 1 : uniform(1, INT32_MAX - 1);
+        const mw::Divisor by(d);
+        for (int k = 0; k < 60; ++k) {
+            const int64_t at = k < 30 ? static_cast<int64_t>(uniform(0, (INT32_MAX - 1) / d)) * d + k % 3 - 1
+                                      : k < 32 ? INT32_MAX - (k - 30) : k < 34 ? k - 32 : uniform(0, INT32_MAX - 1);
+            const int n = static_cast<int>(std::min<int64_t>(std::max<int64_t>(at, 0), INT32_MAX));
+            check(n / by == n / d, "quotient by a reciprocal", it);
+        }
+    }
+}
+
 // The merge of a dual block's two wave groups: no two of the O halves handed
 // over, the (m, l) words and the staged rows (fp32 and bf16) may share a byte or
 // leave their buffers, for there is no barrier between one wave's staging and
@@ -415,6 +430,7 @@ void estimator() {
 int main() {
     planners();
     prefill_sizes();
+    divisors();
     dual_merge();
     dual_order();
     allocator();
