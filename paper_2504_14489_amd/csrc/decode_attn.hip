@@ -3,8 +3,9 @@
 // fixed-chunk split kernel and its combine kernel (their bodies are in
 // decode_block.h), and their launch.
 #include <algorithm>
-#include <climits>
 #include <atomic>
+#include <climits>
+#include <cmath>
 #include <mutex>
 
 #include "decode_block.h"
@@ -155,7 +156,6 @@ mw_status plan_decode(const mw_attn_shape *shape, int32_t batch, const int32_t *
         int64_t np_max = 0;
         for (int32_t b = 0; b < batch; ++b)
             np_max = std::max<int64_t>(np_max, (h_seq_lens[b] + kPageSize - 1) / kPageSize);
-        const int64_t units_bal = (pages + pl->per_unit - 1) / pl->per_unit;
         auto padded_units = [&](int64_t r) {
             int64_t n = 0;
             for (int32_t b = 0; b < batch; ++b) n += ((h_seq_lens[b] + kPageSize - 1) / kPageSize + r - 1) / r;
@@ -180,13 +180,18 @@ mw_status plan_decode(const mw_attn_shape *shape, int32_t batch, const int32_t *
                 // leaves two pieces to merge).  The range is the shortest one,
                 // no shorter than the balanced one, whose padded segments need
                 // no more units than CUs (equal segments are then cut in equal
-                // pieces).  Padding is used only if it leaves at least 70% of
-                // the balanced split's units and 70% of their pages, and
-                // idles no more than 20000 pages (164 MB): over 30 batches of
-                // 1 to 128 sequences of 64 to 32000 tokens it then takes up to
-                // 16% less (128 skewed sequences of one kv head 29.7 -> 24.9
-                // us) and never more, and past these lines up to 5% more (30 of
-                // 16000 to 32000 tokens, 137000 idle pages, 454 -> 476 us).
+                // pieces); longer than the balanced one, it leaves CUs idle.
+                // Padding is used where the longer stream takes less than what
+                // it saves at the end: 3.4 us of second pieces' merges, or 7.5 us
+                // where whole segments leave nothing to merge.  On few CUs a CU
+                // streams at its own limit (0.14 us a page) and the range counts,
+                // on many the memory's (0.00104 us a page of the call): their sum
+                // at the power 11/4, fitted to both splits of 867 batches of 1 to
+                // 252 sequences of 64 to 32768 tokens on 8 to 256 CUs, is 0.2% off
+                // the faster split in the mean and 10% at most.  (Padding by
+                // shares, down to 70% of the units and of their pages, was up to
+                // 56% off: three sequences of 16000, 16000 and 4000 tokens of 8 kv
+                // heads on 32 CUs 146 us, balanced 94.)
                 int64_t lo = pl->per_unit, hi = std::max(np_max, lo);
                 while (lo < hi) {
                     const int64_t mid = lo + (hi - lo) / 2;
@@ -196,9 +201,11 @@ mw_status plan_decode(const mw_attn_shape *shape, int32_t batch, const int32_t *
                         lo = mid + 1;
                 }
                 const int64_t n = padded_units(lo);
-                if (n <= sized + segs - 1 && 10 * n >= 7 * units_bal && 10 * pages >= 7 * n * lo &&
-                    n * lo - pages <= 20000)
-                    align_to(lo);
+                const auto stream_us = [&](int64_t r) {
+                    return std::pow(std::pow(0.14 * r, 2.75) + std::pow(0.00104 * pages, 2.75), 1 / 2.75);
+                };
+                const double saved = lo < np_max ? 3.4 : 7.5;
+                if (n <= sized + segs - 1 && stream_us(lo) < stream_us(pl->per_unit) + saved) align_to(lo);
             }
         }
         pl->units = pl->total > 0 ? (pl->total + pl->per_unit - 1) / pl->per_unit : 0;

@@ -124,6 +124,26 @@ void planners() {
     }
 }
 
+// Three segments whose padding would leave a quarter of the units idle and make
+// ranges 1.8 (32 CUs) and 1.3 times as long: balanced there, where a CU's stream is
+// the bound; padded on the whole GPU, where the memory is and padding is free.
+void padding() {
+    mw_kv_pool_desc desc{1 << 14, 16, 8, 128};
+    mw_kv_pool *pool = nullptr;
+    check(mw_kv_pool_create(&desc, g_fake, g_fake, &pool) == MW_OK, "pool create", -1);
+    const mw_attn_shape shape{32, 8, 128, 0.0883883f};
+    const int32_t lens[3] = {16000, 16000, 4000};
+    mw_decode_args a{pool, shape, 3, lens, reinterpret_cast<int32_t *>(g_fake), reinterpret_cast<int32_t *>(g_fake),
+                     1000, g_fake, g_fake, g_fake, ~size_t{0}, 0};
+    mw::DecodePlan dp;
+    for (int cus : {32, 64, 256}) {
+        check(mw::decode_prepare(&a, cus, &dp, "decode_prepare") == MW_OK, "plan", cus);
+        check(dp.aligned == (cus == 256), "padding by time", cus);
+        check(dp.aligned || dp.units == cus, "a unit per CU", cus);
+    }
+    mw_kv_pool_destroy(pool);
+}
+
 // Sizes of calls far past any pool: every length that the size call accepts, with
 // groups whose rows no longer fit 32 bits.
 void prefill_sizes() {
@@ -429,6 +449,7 @@ void estimator() {
 
 int main() {
     planners();
+    padding();
     prefill_sizes();
     divisors();
     dual_merge();
