@@ -280,8 +280,12 @@ mw_status mw_prefill_workspace_size(const mw_attn_shape *shape, int32_t batch, c
                                     const int32_t *h_prefix_lens, int32_t num_cus, size_t *bytes);
 /* Arguments as mw_prefill_attn, plus d_workspace (device, 16-B aligned,
  * caller-owned, contents need not be initialised) of workspace_bytes.
- * MW_ERR_INVALID_ARG if the split this call makes needs more workspace than
- * given (the size call with this stream's CU count, or with 0, suffices). */
+ * The size call with this stream's CU count, or with 0, suffices.  With less the
+ * call makes as many pieces as fit, or none; MW_ERR_INVALID_ARG only if it is short
+ * also of the pieces of blocks of 32 positions x up to four query heads: with
+ * fewer such blocks than CUs (and more than 4 key tiles), min(8, max(2, 2 CUs /
+ * blocks)) pieces of at least 4 tiles, with fewer than two per CU 3 where a block
+ * has 96 tiles and more, none on larger grids. */
 mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_shape *shape, int32_t batch,
                              const int32_t *h_new_lens, const int32_t *h_prefix_lens,
                              const int32_t *d_qo_indptr, const int32_t *d_prefix_lens,

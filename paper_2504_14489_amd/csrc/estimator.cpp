@@ -276,6 +276,18 @@ PrefillLaunch prefill_launch(int32_t batch, const int32_t *nl, const int32_t *rl
     return {pl.waves == 4 ? 1 : 0, t_max * static_cast<double>(cus) / total};
 }
 
+}  // namespace
+
+int mw::prefill_base_pieces(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hkv, int group,
+                            int64_t cus) {
+    const int64_t heads = static_cast<int64_t>(hkv) * ((group + 3) / 4);
+    Modelled m = model_launch(batch, h_new_lens, heads, cus);
+    if (m.waves == 4) model_split(batch, h_new_lens, h_prefix_lens, heads, cus, &m);
+    return m.pieces;
+}
+
+namespace {
+
 int cell(int64_t x, int64_t base) {
     int k = 0;
     for (int64_t v = 1; v < x; v *= base) ++k;

@@ -161,9 +161,22 @@ struct PrefillPlan {
 mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who,
                           bool split = false);
 // Plans body, order and key-range split of a call on `cus` CUs from its lengths
-// (cus = 0: only the largest split any stream could take); hkv and group must be
-// set, lengths must have been validated.
+// (cus = 0: only the largest split any stream could take), with no more pieces
+// than fit workspace_bytes; hkv and group must be set, lengths must have been
+// validated.
 void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hq,
-                        int64_t cus, PrefillPlan *p);
+                        int64_t cus, PrefillPlan *p, size_t workspace_bytes = ~size_t{0});
+// Plans again if the caller's workspace is short of what the plan wants, with as
+// many pieces as it holds, or none.  MW_ERR_INVALID_ARG where it is also short of
+// what callers have always brought: prefill_base_pieces.
+mw_status prefill_fit_workspace(const mw_prefill_args *a, int64_t cus, PrefillPlan *p, const void *ws, size_t bytes,
+                                const char *who);
+// Pieces of a call on blocks of 32 positions x up to four query heads (1: none):
+// with fewer of them than CUs, so many that two work-groups come on a CU; with
+// fewer than two per CU, three for blocks of 96 tiles and more.  A caller that
+// plans for those knows no other calls to need a workspace.  (estimator.cpp,
+// whose modelled launch they belong to.)
+int prefill_base_pieces(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hkv, int group,
+                        int64_t cus);
 
 }  // namespace mw

@@ -314,7 +314,7 @@ int64_t big_units(const CallJobs &c, int64_t cus, const PrefillPlan &p) {
 namespace mw {
 
 void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t *h_prefix_lens, int hq,
-                        int64_t cus, PrefillPlan *p) {
+                        int64_t cus, PrefillPlan *p, size_t workspace_bytes) {
     p->pieces = 1;
     p->piece_tiles = 0;
     p->split_bytes = 0;
@@ -351,12 +351,12 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     // tiles and more, and blocks of 10 tiles and more of which four pieces each
     // fit the CUs at once (whole ones are up to 2 us faster at 10 to 13 tiles, and
     // 1 to 5 us slower from 15).
-    const bool cuttable = c.two8.n < cus && j.n < 2 * cus;
+    const bool cuttable = c.two8.n < cus && j.n < 2 * cus && bytes_for(2) <= workspace_bytes;
     const bool must_cut = cuttable && (max_nt >= 96 || (4 * j.n <= cus && max_nt >= 10));
     double best = must_cut ? INFINITY : plain;
     for (int k = must_cut ? 2 : 1; k <= (cuttable ? kPrefillMaxPieces : 1); ++k) {
         const int pt = std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k);
-        if (k > 1 && pt >= max_nt) break;
+        if (k > 1 && (pt >= max_nt || bytes_for(prefill_pieces(max_nt, pt, kPrefillMaxPieces)) > workspace_bytes)) break;
         Jobs jk = j;
         double merge = 0.0;
         if (k > 1) {
@@ -381,6 +381,21 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     if (!p->dual || p->piece_tiles == 0) return;
     p->pieces = prefill_pieces(max_nt, p->piece_tiles, kPrefillMaxPieces);
     p->split_bytes = bytes_for(p->pieces);
+}
+
+mw_status prefill_fit_workspace(const mw_prefill_args *a, int64_t cus, PrefillPlan *p, const void *ws, size_t bytes,
+                                const char *who) {
+    const size_t usable = ws && aligned16(ws) ? bytes : 0;
+    if (usable >= p->split_bytes) return MW_OK;
+    const int hq = p->hkv * p->group;
+    const int pieces = prefill_base_pieces(a->batch, a->h_new_lens, a->h_prefix_lens, p->hkv, p->group, cus);
+    const size_t least =
+        pieces > 1 ? static_cast<size_t>(pieces) * p->rows * hq * (kHeadDim * 4 + 8) : 0;
+    if (usable < std::min(least, p->split_bytes))
+        return fail(MW_ERR_INVALID_ARG, "%s: the split needs a 16-byte aligned workspace of %zu bytes (got %zu)", who,
+                    p->split_bytes, ws && !aligned16(ws) ? size_t{0} : bytes);
+    prefill_split_plan(a->batch, a->h_new_lens, a->h_prefix_lens, hq, cus, p, usable);
+    return MW_OK;
 }
 
 mw_status prefill_prepare(const mw_prefill_args *a, int64_t cus, bool allow_small, PrefillPlan *p, const char *who,
@@ -497,6 +512,7 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
     PrefillPlan pl;
     const int64_t cus = stream_cus(s);
     mw_status st = prefill_prepare(&a, cus, true, &pl, who, true);
+    if (st == MW_OK) st = prefill_fit_workspace(&a, cus, &pl, d_workspace, workspace_bytes, who);
     if (st != MW_OK) return st;
     if (pl.big_units > 0) {
         const int64_t n_big = pl.big_units, units = pl.gx;
@@ -515,9 +531,6 @@ extern "C" mw_status mw_prefill_attn_ws(const mw_kv_pool *pool, const mw_attn_sh
     }
     if (!pl.dual) return launch_plain(a, pl, s, timing);
     const bool cut = pl.pieces > 1;
-    if (cut && (!d_workspace || !aligned16(d_workspace) || workspace_bytes < pl.split_bytes))
-        return fail(MW_ERR_INVALID_ARG, "%s: the split needs a 16-byte aligned workspace of %zu bytes (got %zu)",
-                    who, pl.split_bytes, workspace_bytes);
     int64_t max_n = 0;
     for (int32_t b = 0; b < batch; ++b) max_n = std::max<int64_t>(max_n, h_new_lens[b]);
     st = timing_begin(timing, s);

@@ -124,6 +124,51 @@ void planners() {
     }
 }
 
+// A prefill workspace short of the plan's pieces: fewer pieces that fit, or none;
+// refused only if short of what blocks of 32 positions need as well.
+void short_workspaces() {
+    mw_kv_pool_desc desc{1 << 14, 16, 1, 128};
+    int fewer = 0, none = 0, refused = 0;
+    for (int it = 0; it < 3000; ++it) {
+        const int hkv = 1 << uniform(0, 3), group = uniform(1, 16), batch = uniform(1, 16);
+        desc.num_kv_heads = hkv;
+        mw_kv_pool *pool = nullptr;
+        check(mw_kv_pool_create(&desc, g_fake, g_fake, &pool) == MW_OK, "pool create", it);
+        std::vector<int32_t> n(batch), r(batch);
+        const int n_hi = 1 << uniform(0, 11), r_hi = 1 << uniform(0, 14);
+        for (int b = 0; b < batch; ++b) n[b] = uniform(1, n_hi), r[b] = uniform(0, r_hi);
+        const mw_prefill_args a{pool, {hkv * group, hkv, 128, 0.0883883f}, batch, n.data(), r.data(),
+                                reinterpret_cast<int32_t *>(g_fake), reinterpret_cast<int32_t *>(g_fake),
+                                reinterpret_cast<int32_t *>(g_fake), (n_hi + r_hi + 15) / 16, g_fake, g_fake};
+        const int cus = 8 * uniform(1, 32);
+        mw::PrefillPlan want;
+        check(mw::prefill_prepare(&a, cus, true, &want, "prepare", true) == MW_OK, "plan", it);
+        const int base = mw::prefill_base_pieces(batch, n.data(), r.data(), hkv, group, cus);
+        const size_t piece = static_cast<size_t>(want.rows) * hkv * group * (mw::kHeadDim * 4 + 8);
+        check(base >= 1 && base <= mw::kPrefillMaxPieces, "base pieces", it);
+        for (int given = 0; given <= mw::kPrefillMaxPieces; ++given) {
+            mw::PrefillPlan p = want;
+            // with no pieces: a missing, a misaligned or an empty workspace
+            const void *ws = given ? g_fake : it % 3 == 0 ? nullptr : g_fake + (it % 3 == 1 ? 8 : 0);
+            const size_t bytes = given ? given * piece : it % 3 == 1 ? 100 * piece : 0;
+            const mw_status st = mw::prefill_fit_workspace(&a, cus, &p, ws, bytes, "fit");
+            const int wanted = want.pieces > 1 ? want.pieces : 0, least = std::min(wanted, base > 1 ? base : 0);
+            check((st == MW_OK) == (given >= least), "accepted with what callers bring", it);
+            if (st != MW_OK) {
+                ++refused;
+                continue;
+            }
+            check(p.split_bytes <= given * piece || (given >= wanted && p.split_bytes == want.split_bytes),
+                  "pieces fit the workspace", it);
+            check(p.pieces == 1 || (p.dual && p.pieces * piece == p.split_bytes), "pieces and bytes", it);
+            check(p.gx > 0 && p.gy >= 1 && (given < wanted || p.pieces == want.pieces), "launch", it);
+            if (given < wanted) ++(p.pieces > 1 ? fewer : none);
+        }
+        mw_kv_pool_destroy(pool);
+    }
+    check(fewer > 10 && none > 10 && refused > 100, "short workspaces of every kind", fewer);
+}
+
 // Three segments whose padding would leave a quarter of the units idle and make
 // ranges 1.8 (32 CUs) and 1.3 times as long: balanced there, where a CU's stream is
 // the bound; padded on the whole GPU, where the memory is and padding is free.
@@ -449,6 +494,7 @@ void estimator() {
 
 int main() {
     planners();
+    short_workspaces();
     padding();
     prefill_sizes();
     divisors();

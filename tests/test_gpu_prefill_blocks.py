@@ -15,10 +15,11 @@ from tests.test_gpu_prefill import _varlen_setup
 pytestmark = pytest.mark.gpu
 
 
-def _run(hq, hkv, seqs, cus, seed, bad_from=None):
+def _run(hq, hkv, seqs, cus, seed, bad_from=None, ws_pieces=None):
     """The batch through the split-enabled and the plain entry point on the
     prefill stream of `cus` CUs (0: the whole GPU); every row of both against
-    the oracle.  bad_from: the one sequence's values from this token on are NaN or
+    the oracle.  ws_pieces: the workspace holds this many pieces (0: none is
+    passed) instead of the most any stream can need.  bad_from: the one sequence's values from this token on are NaN or
     infinite, and only rows that may not depend on them are compared."""
     wls, k, v, bt, stride, q = _varlen_setup(seqs, hq, hkv, seed)
     if bad_from is not None:
@@ -37,13 +38,16 @@ def _run(hq, hkv, seqs, cus, seed, bad_from=None):
     try:
         stream = part.prefill_stream if part else 0
         nbytes = mw.mw_prefill_workspace_size(hq, hkv, 128, ns, rs, 0)
+        if ws_pieces is not None:
+            nbytes = ws_pieces * sum(ns) * hq * 520
         ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev)
+        ws_args = (ws.data_ptr() if nbytes else 0, nbytes)
         for split in (True, False):
             do = torch.zeros_like(dq)
             args = (pool, hq, hkv, 128, 1 / np.sqrt(128), ns, rs, indptr.data_ptr(), pref.data_ptr(), dbt.data_ptr(),
                     stride, dq.data_ptr(), do.data_ptr())
             if split:
-                mw.mw_prefill_attn_ws(*args, ws.data_ptr(), ws.numel(), stream)
+                mw.mw_prefill_attn_ws(*args, *ws_args, stream)
             else:
                 mw.mw_prefill_attn(*args, stream)
             torch.cuda.synchronize()
@@ -130,3 +134,23 @@ def test_prefill_last_round_in_halves(hq, hkv, seqs):
 def test_prefill_later_values_not_finite(hq, hkv, r, n, bad_from, cus):
     say(f"prefill later values not finite hq={hq} hkv={hkv} r={r} n={n} from {bad_from} cus={cus}")
     _run(hq, hkv, [(r, n)], cus, 1700 + n, bad_from)
+
+
+# workspaces short of the pieces the plan would take: none where blocks of 32
+# positions x four heads are more than the CUs (the call runs uncut), three pieces
+# of four; and none for a call that has always been cut, which is refused
+@pytest.mark.parametrize("hq,hkv,seqs,cus,wanted,given", [
+    (16, 1, [(3314, 181), (1958, 168), (3991, 269), (4818, 125), (3609, 73), (5154, 229), (7218, 221), (3371, 200),
+             (3815, 106), (5246, 118), (7240, 170), (6627, 73)], 128, 2, 0),
+    (32, 8, [(10732, 3), (8417, 4), (4165, 3)], 32, 4, 3)])
+def test_prefill_short_workspace(hq, hkv, seqs, cus, wanted, given):
+    say(f"prefill short workspace hq={hq} hkv={hkv} {seqs} cus={cus}")
+    ns, rs = [n for _, n in seqs], [r for r, _ in seqs]
+    assert mw.mw_prefill_workspace_size(hq, hkv, 128, ns, rs, cus) == wanted * sum(ns) * hq * 520
+    _run(hq, hkv, seqs, cus, 2100, ws_pieces=given)
+
+
+def test_prefill_missing_workspace_is_refused():
+    with pytest.raises(mw.MWError) as e:
+        _run(8, 1, [(6144, 2048)], 96, 2200, ws_pieces=0)
+    assert e.value.status == mw.MW_ERR_INVALID_ARG
