@@ -332,8 +332,10 @@ class Bench:
 
 
 # ------------------------------------------------------------- rooflines --
-KERNEL_SOURCES = {"k_prefill_attn": ("prefill_attn.hip", "prefill_block.h"),
-                  "k_decode_balanced": ("decode_attn.hip", "decode_block.h")}
+PREFILL_KERNELS = ("k_prefill_attn", "k_prefill_dual", "k_prefill_mixed")  # of a prefill call of one launch
+KERNEL_SOURCES = {"k_decode_balanced": ("decode_attn.hip", "decode_block.h"),
+                  **{k: ("prefill_attn.hip", "prefill_block.h", "prefill_layout.h", "prefill_schedule.h")
+                     for k in PREFILL_KERNELS}}
 
 
 def source_sha(kernel):
@@ -371,10 +373,14 @@ def roofline_entries(b, res):
     n_launch = len(b.chunks)
     pre_ms = res["mux"]["prefill_kernel_ms"] / n_launch
     dec_ms = res["mux"]["decode_kernel_ms"]
-    # a call of one launch is listed under the plain kernel whichever body the
-    # plan took; a key-range split is two
-    split = res["mux"]["prefill_kernels"] > 1
-    pre = {"kernel": "k_prefill_dual+k_prefill_merge" if split else "k_prefill_attn", "bound": "mfma",
+    # a key-range split is two launches; which kernel a call of one takes is the
+    # plan's choice, and known here where a committed profile of it has it
+    if res["mux"]["prefill_kernels"] > 1:
+        pre_kernel = "k_prefill_dual+k_prefill_merge"
+    else:
+        known = [k for k in PREFILL_KERNELS if committed_traffic(k, b.cfg.name) is not None]
+        pre_kernel = known[0] if len(known) == 1 else "|".join(PREFILL_KERNELS)
+    pre = {"kernel": pre_kernel, "bound": "mfma",
            "unit": "TFLOP/s",
            "achieved": b.pre_flop / n_launch / (pre_ms * 1e-3) / 1e12, "peak": BF16_PEAK_TFLOPS,
            "work_per_launch": b.pre_flop / n_launch, "work_unit": "FLOP", "kernel_ms": pre_ms,

@@ -383,15 +383,20 @@ mw_status mw_decode_attn_noalloc(const mw_kv_pool *pool, const mw_attn_shape *sh
  *       MW_ERR_INVALID_ARG).  A single attention call, unlike the paper's
  *       whole-model iterations, keeps the steps of its launch: rounds of
  *       work-groups over the partition's CUs, and calls whose few work-groups
- *       run at once, bound by the longest.  With the shape, each prefill
- *       call's launch on `cus` CUs is planned as mw_prefill_attn_ws plans it
- *       (key-range split included) and simulated: the work-groups in dispatch
+ *       run at once, bound by the longest.  With the shape, a model launch of
+ *       each prefill call on `cus` CUs is simulated: blocks of 64 positions x up
+ *       to four query heads or, where pairs of those would not give every CU
+ *       one, of 32, two per CU, cut by key range where they are few.  It has the
+ *       steps of a launch but is not the one mw_prefill_attn_ws makes, whose
+ *       bodies, order and pieces follow measured costs and whose blocks hold 256
+ *       or 128 rows of any group (for groups that are no multiple of 4 the model
+ *       has more blocks).  The work-groups go in dispatch
  *       order, each to a CU slot that frees within 5% of the mean
  *       work-group's work of the earliest one, preferring the CU that holds
  *       the fewest work-groups so far (work-groups a tile or two apart finish
  *       together), a work-group's work its key tiles.  The n^2, n r and n terms of Eq. (1) are multiplied by the
  *       load-imbalance factor (the latest CU's time over the time of the same
- *       work spread evenly), and the kernel path (8-wave or 4-wave blocks)
+ *       work spread evenly), and the model's path (8-wave or 4-wave blocks)
  *       selects one of two models per partition size, fitted separately, as
  *       the paper keeps separate models for separate kernels.  Predicting
  *       with a path whose model is not fitted uses the other path's model;

@@ -52,13 +52,21 @@ __host__ __device__ inline int prefill_pieces(int nt, int piece_tiles, int max_p
     return k < 1 ? 1 : (k > max_pieces ? max_pieces : k);
 }
 // Key tiles (64 keys) of query block q of a sequence with prefix r and n new
-// tokens: blocks of `block_rows` rows of n x group queries (by default 32
-// positions).  T: the type of the row counts; 32 bits hold those of a call that
+// tokens: blocks of `block_rows` rows of its n x group queries.  T: the type of the row counts; 32 bits hold those of a call that
 // fits the device's memory, but not of every length a caller may ask a size for.
 template <class T = int>
-__host__ __device__ inline int prefill_block_tiles(T r, T n, T q, T block_rows = 32, T group = 1) {
+__host__ __device__ inline int prefill_block_tiles(T r, T n, T q, T block_rows, T group) {
     const T end = (q + 1) * block_rows < n * group ? (q + 1) * block_rows : n * group;
     return static_cast<int>((r + (end + group - 1) / group + 63) / 64);
+}
+
+// Blocks of t or more key tiles among the nqb blocks of `block_rows` rows of a
+// sequence.  A block that ends with row e reads r + ceil(e / group) keys, so it has
+// t tiles of 64 or more when e > (64 (t - 1) - r) group: the sequence's last blocks,
+// counted without dividing by the group.
+__host__ __device__ inline int prefill_blocks_at_least(int nqb, int n, int r, int group, int block_rows, int t) {
+    const int c = 64 * (t - 1) - r;
+    return c < 0 ? nqb : c >= n ? 0 : nqb - static_cast<int>(static_cast<unsigned>(c * group) / static_cast<unsigned>(block_rows));
 }
 
 // Number of CUs a stream's kernels may run on (its CU mask; all CUs of the

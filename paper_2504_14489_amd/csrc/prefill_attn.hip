@@ -64,7 +64,11 @@ k_prefill_mixed(const uint16_t *__restrict__ kpool, const uint16_t *__restrict__
                 const int32_t *__restrict__ qo_indptr, const int32_t *__restrict__ prefix_lens,
                 const int32_t *__restrict__ bt, int bt_stride, int batch, Divisor hkv, Divisor group, int num_pages,
                 float scale_log2, int order, int n_big) {
-#ifdef __HIP_DEVICE_COMPILE__  // the host pass refuses a second use of one prefill_block instantiation
+    // Device pass only: clang's host pass, whose code for a kernel is a stub in any
+    // case, refuses the second use of an instantiation that k_prefill_attn has used
+    // ("no matching function for call to 'prefill_block' ... candidate template
+    // ignored: substitution failure", with no reason given).
+#ifdef __HIP_DEVICE_COMPILE__
     __shared__ __attribute__((aligned(1024))) uint16_t s_k[4 * TILE];
     __shared__ __attribute__((aligned(1024))) uint16_t s_v[4 * TILE];
     __shared__ int32_t s_bt[kBtCache];

@@ -45,7 +45,7 @@
 //                            taken straight from the S^T accumulators as bf16
 // Online softmax in base 2 (scores scaled by scale*log2 e inside one FMA); the
 // causal mask is applied only on tiles that cross the diagonal; row sums are
-// taken over the bf16 probabilities the PV product uses.  The running
+// taken in fp32 over the probabilities before they are rounded to bf16 for PV.  The running
 // maximum moves only when a column's tile maximum exceeds it by more than 2^8
 // (O and l are then rescaled); O / l does not depend on the reference maximum.
 // O is staged through LDS so that each store writes whole 256-byte rows.
@@ -177,18 +177,15 @@ __device__ __forceinline__ bool work_item(const int32_t *__restrict__ qo_indptr,
     it.kvh = x - j * hkv;
     it.blk2 = -1;
     if (order == kSorted && batch > 1) {
-        // lane i: sequence i.  A block of e rows' end reads r + ceil(e / group)
-        // keys, so it has at least T tiles of 64 when e > (64 (T - 1) - r) group:
-        // the last blocks of the sequence, counted without a division.
+        // lane i: sequence i
         const int lane = threadIdx.x & 63;
         const bool in = lane < batch;
         const int first = in ? qo_indptr[lane] : 0;
         const int n = in ? qo_indptr[lane + 1] - first : 0;
         const int r = in ? prefix_lens[lane] : 0;
         const int nqb = (n * group + kBR - 1) / kBR;
-        auto at_least = [&](int t) __attribute__((always_inline)) {  // blocks of t tiles or more
-            const int c = BN * (t - 1) - r;
-            return c < 0 ? nqb : c >= n ? 0 : nqb - static_cast<int>(static_cast<unsigned>(c * group) / kBR);
+        auto at_least = [&](int t) __attribute__((always_inline)) {
+            return prefill_blocks_at_least(nqb, n, r, group, kBR, t);
         };
         auto total = [&](int v) __attribute__((always_inline)) {
             return __builtin_amdgcn_readlane(wave_scan(v), 63);

@@ -152,13 +152,13 @@ def pair_slowdown(pre: PrefillCall, dec: DecodeCall, part: Partition, pre_ms: fl
 
 
 def work_groups(sample, phase) -> int:
-    """Work-groups of the call: query blocks of 64 positions x kv heads for
-    prefill; for decode the balanced split's page ranges (two per CU, at
-    least 16 pages each)."""
+    """Work-groups of the call: query blocks of 256 rows x kv heads for prefill
+    (a row is one query head of a position); for decode the balanced split's page
+    ranges (one per CU, at least 16 pages each)."""
     if phase == 0:
-        return (sample["n"] + 63) // 64 * HKV
+        return (sample["n"] * (HQ // HKV) + 255) // 256 * HKV
     pages = sum((L + PAGE - 1) // PAGE for L in sample["lens"]) * HKV
-    return min(2 * sample["cus"], (pages + 15) // 16)
+    return min(sample["cus"], (pages + 15) // 16)
 
 
 def write_table(result, path, command):

@@ -6,6 +6,11 @@
         --title "..." --command "..." --out profiles/kernel_trace_llama8b.md
     python -m paper_2504_14489_amd.rocprof_summary mfma --dir <dir of the MFMA counter run> --workload llama8b \\
         --cus 64 --out profiles/mfma_llama8b.txt
+    python -m paper_2504_14489_amd.rocprof_summary run --case prefill_2k
+
+The last runs one step of a measured case (perf/cases.py) and the calibrating
+copy, to be profiled; ``traffic`` and ``mfma`` then take ``--case prefill_2k`` in the
+place of a workload.
 
 The traffic summary scales each kernel's FETCH_SIZE / WRITE_SIZE (KiB per
 dispatch) by what the same counter reads for the runtime's device copy of a
@@ -63,9 +68,41 @@ def counter_per_dispatch(d: str, counter: str):
     return out
 
 
+def option(args) -> str:
+    return f"--case {args.case}" if args.case else f"--workload {args.workload}"
+
+
+def subject(args):
+    """What the counters were collected on, and the program that ran it."""
+    if args.case:
+        return (f"one step of the case {args.case}",
+                f"python3 -m paper_2504_14489_amd.rocprof_summary run --case {args.case}")
+    return f"{args.workload} workload", f"python3 bench.py --config {args.workload} --traffic-pass"
+
+
+def measured_case(name):
+    from perf import cases
+    return cases, next(c for c in cases.listed() if c["name"] == name)
+
+
+def run(args):
+    import torch
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    cases, case = measured_case(args.case)
+    state = cases.prepare(case, 1)
+    torch.cuda.synchronize()
+    cases.run(state)
+    torch.cuda.synchronize()
+    src = torch.empty(COPY_BYTES, dtype=torch.uint8, device="cuda")
+    torch.empty_like(src).copy_(src)
+    torch.cuda.synchronize()
+    print(f"one step of {args.case} and a copy of {COPY_BYTES} bytes done", flush=True)
+
+
 def traffic(args):
     sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     from bench import source_sha, KERNEL_SOURCES
+    what, program = subject(args)
     fetch = counter_per_dispatch(args.fetch, "FETCH_SIZE")
     write = counter_per_dispatch(args.write, "WRITE_SIZE")
     if COPY_KERNEL not in fetch or COPY_KERNEL not in write:
@@ -75,15 +112,13 @@ def traffic(args):
     # the workload's small arrays)
     f_copy, w_copy = max(fetch[COPY_KERNEL]), max(write[COPY_KERNEL])
     f_scale, w_scale = kib / f_copy, kib / w_copy
-    lines = [f"# HBM traffic per launch: {args.workload} workload", "",
+    lines = [f"# HBM traffic per launch: {what}", "",
              "Commands (on the MI355X box, from /tmp with TMPDIR=/tmp; one counter per run):", "",
-             f"    rocprofv3 --pmc FETCH_SIZE --output-format csv -d {args.fetch} -o run -- "
-             f"python3 bench.py --config {args.workload} --traffic-pass",
-             f"    rocprofv3 --pmc WRITE_SIZE --output-format csv -d {args.write} -o run -- "
-             f"python3 bench.py --config {args.workload} --traffic-pass",
-             f"    python -m paper_2504_14489_amd.rocprof_summary traffic --workload {args.workload} "
+             f"    rocprofv3 --pmc FETCH_SIZE --output-format csv -d {args.fetch} -o run -- {program}",
+             f"    rocprofv3 --pmc WRITE_SIZE --output-format csv -d {args.write} -o run -- {program}",
+             f"    python -m paper_2504_14489_amd.rocprof_summary traffic {option(args)} "
              f"--fetch {args.fetch} --write {args.write} --out <this file>", "",
-             "bench.py --traffic-pass runs one isolated launch of each kernel on its partition and a "
+             "The program runs one isolated launch of each kernel and a "
              f"device-to-device copy of {COPY_BYTES} bytes ({COPY_KERNEL}) that calibrates the counters.", "",
              f"# copy calibration: FETCH_SIZE read {f_copy:.1f} KiB and WRITE_SIZE {w_copy:.1f} KiB for "
              f"{kib:.0f} KiB moved",
@@ -105,39 +140,47 @@ def traffic(args):
 
 
 def mfma(args):
-    """Matrix-core use of k_prefill_attn from SQ_INSTS_VALU_MFMA_MOPS_BF16 (512 flop
-    each), SQ_VALU_MFMA_BUSY_CYCLES (summed over SIMDs) and GRBM_GUI_ACTIVE."""
+    """Matrix-core use of the prefill kernels from SQ_INSTS_VALU_MFMA_MOPS_BF16 (512
+    flop each), SQ_VALU_MFMA_BUSY_CYCLES (summed over SIMDs) and GRBM_GUI_ACTIVE."""
     sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
-    from bench import source_sha
+    from bench import PREFILL_KERNELS, source_sha
     from paper_2504_14489_amd import accounting, workloads as W
-    cfg = W.CONFIGS[args.workload]
+    if args.case:
+        cases, case = measured_case(args.case)
+        pre = {k: v for k, v in case.items() if k != "dec_batch"}
+        algo, part = cases.work(pre)["flops"], "its prefill"
+    else:
+        cfg = W.CONFIGS[args.workload]
+        algo = accounting.prefill_flops(cfg.hq, cfg.head_dim, [cfg.pre_chunks[0]])
+        part = "first prefill chunk"
     vals = {c: counter_per_dispatch(args.dir, c) for c in
             ("SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_VALU_MFMA_BUSY_CYCLES", "GRBM_GUI_ACTIVE")}
-    k = "k_prefill_attn"
-    mops = statistics.median(vals["SQ_INSTS_VALU_MFMA_MOPS_BF16"][k])
-    busy = statistics.median(vals["SQ_VALU_MFMA_BUSY_CYCLES"][k])
-    # the CSV sums GRBM_GUI_ACTIVE over the 8 XCDs; each XCD counts the same
-    # dispatch, so one XCD's count is the dispatch's duration in cycles
-    active = statistics.median(vals["GRBM_GUI_ACTIVE"][k]) / N_XCD
-    algo = accounting.prefill_flops(cfg.hq, cfg.head_dim, [cfg.pre_chunks[0]])
     simds = 4 * args.cus
-    lines = [f"# Matrix-core use of k_prefill_attn: {args.workload} workload, first prefill chunk on {args.cus} CUs",
+    what, program = subject(args)
+    lines = [f"# Matrix-core use of prefill: {what}, {part} on {args.cus} CUs",
              "", "Commands (on the MI355X box, from /tmp with TMPDIR=/tmp):", "",
              f"    rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_VALU_MFMA_BUSY_CYCLES GRBM_GUI_ACTIVE "
-             f"--output-format csv -d {args.dir} -o run -- python3 bench.py --config {args.workload} "
-             f"--traffic-pass",
-             f"    python -m paper_2504_14489_amd.rocprof_summary mfma --dir {args.dir} --workload "
-             f"{args.workload} --cus {args.cus} --out <this file>", "",
-             f"k_prefill_attn.mfma_bf16_flop: {mops * 512:.0f}",
-             f"k_prefill_attn.algorithmic_flop: {algo:.0f}",
-             f"k_prefill_attn.executed_over_algorithmic: {mops * 512 / algo:.4f}",
-             f"k_prefill_attn.mfma_busy_cycles_sum: {busy:.0f}",
-             f"k_prefill_attn.gui_active_cycles_per_xcd: {active:.0f}",
-             f"k_prefill_attn.mfma_busy_fraction_of_partition_simds: {busy / (active * simds):.4f}",
-             f"k_prefill_attn.source_sha256_16: {source_sha(k)}", "",
-             "executed / algorithmic > 1: the MFMAs of masked key tiles on the diagonal and of padding rows.",
-             "busy fraction: SQ_VALU_MFMA_BUSY_CYCLES over GRBM_GUI_ACTIVE times the partition's SIMDs "
-             f"({simds}).", ""]
+             f"--output-format csv -d {args.dir} -o run -- {program}",
+             f"    python -m paper_2504_14489_amd.rocprof_summary mfma --dir {args.dir} {option(args)} "
+             f"--cus {args.cus} --out <this file>", ""]
+    for k in PREFILL_KERNELS:
+        if not vals["GRBM_GUI_ACTIVE"].get(k):
+            continue
+        mops = statistics.median(vals["SQ_INSTS_VALU_MFMA_MOPS_BF16"][k])
+        busy = statistics.median(vals["SQ_VALU_MFMA_BUSY_CYCLES"][k])
+        # the CSV sums GRBM_GUI_ACTIVE over the 8 XCDs; each XCD counts the same
+        # dispatch, so one XCD's count is the dispatch's duration in cycles
+        active = statistics.median(vals["GRBM_GUI_ACTIVE"][k]) / N_XCD
+        lines += [f"{k}.mfma_bf16_flop: {mops * 512:.0f}",
+                  f"{k}.algorithmic_flop: {algo:.0f}",
+                  f"{k}.executed_over_algorithmic: {mops * 512 / algo:.4f}",
+                  f"{k}.mfma_busy_cycles_sum: {busy:.0f}",
+                  f"{k}.gui_active_cycles_per_xcd: {active:.0f}",
+                  f"{k}.mfma_busy_fraction_of_partition_simds: {busy / (active * simds):.4f}",
+                  f"{k}.source_sha256_16: {source_sha(k)}", ""]
+    lines += ["executed / algorithmic > 1: the MFMAs of masked key tiles on the diagonal and of padding rows.",
+              "busy fraction: SQ_VALU_MFMA_BUSY_CYCLES over GRBM_GUI_ACTIVE times the partition's SIMDs "
+              f"({simds}).", ""]
     with open(args.out, "w") as f:
         f.write("\n".join(lines))
     print("\n".join(lines))
@@ -213,7 +256,8 @@ def main(argv=None):
     ap = argparse.ArgumentParser(description=__doc__.split("\n\n")[0])
     sub = ap.add_subparsers(dest="cmd", required=True)
     t = sub.add_parser("traffic")
-    t.add_argument("--workload", required=True)
+    t.add_argument("--workload")
+    t.add_argument("--case")
     t.add_argument("--fetch", required=True)
     t.add_argument("--write", required=True)
     t.add_argument("--out", required=True)
@@ -223,17 +267,22 @@ def main(argv=None):
     k.add_argument("--command", required=True)
     k.add_argument("--trace-last", type=int, default=0)
     k.add_argument("--skip-last", type=int, default=0)
-    k.add_argument("--kernels", default="k_prefill_attn,k_decode_balanced")
+    k.add_argument("--kernels", default="k_prefill_attn,k_prefill_dual,k_prefill_mixed,k_prefill_merge,k_decode_balanced")
     k.add_argument("--note", default="")
     k.add_argument("--regions", action="store_true", help="durations inside the regions bench.py marked")
     k.add_argument("--out", required=True)
     m = sub.add_parser("mfma")
     m.add_argument("--dir", required=True)
-    m.add_argument("--workload", required=True)
+    m.add_argument("--workload")
+    m.add_argument("--case")
     m.add_argument("--cus", type=int, required=True)
     m.add_argument("--out", required=True)
+    c = sub.add_parser("run")
+    c.add_argument("--case", required=True)
     args = ap.parse_args(argv)
-    {"traffic": traffic, "trace": trace, "mfma": mfma}[args.cmd](args)
+    if args.cmd in ("traffic", "mfma") and bool(args.workload) == bool(args.case):
+        ap.error("one of --workload and --case")
+    {"traffic": traffic, "trace": trace, "mfma": mfma, "run": run}[args.cmd](args)
 
 
 if __name__ == "__main__":

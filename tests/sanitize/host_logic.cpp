@@ -82,7 +82,7 @@ void planners() {
                     padded += (static_cast<int64_t>(lens[b] + 15) / 16 + dp.per_unit - 1) / dp.per_unit * dp.per_unit;
                 check(dp.per_unit >= 16 && dp.total == padded * hkv && dp.units * dp.per_unit == dp.total,
                       "aligned split covers every padded segment in whole ranges", it);
-                check(cus > 0 && dp.units <= std::min<int64_t>(2 * cus, 512), "aligned split within the units", it);
+                check(cus > 0 && dp.units <= std::min<int64_t>(cus, 256), "aligned split within a unit per CU", it);
             }
         }
         if (st != MW_OK) check(st2 != MW_OK, "a refused size is refused by the plan too", it);
@@ -104,24 +104,110 @@ void planners() {
         if (mw::prefill_prepare(&p, pcus, uniform(0, 1), &pp, "prefill_prepare") == MW_OK) {
             check(pp.gx >= 0 && (pp.waves == 4 || pp.waves == 8) && pp.group == group, "prefill plan", it);
             // the key-range split: at most the pieces the size call with no CU
-            // count allows, pieces of at least 4 tiles, never cut 8-wave launches
+            // count allows, pieces of at least 4 tiles, only of dual blocks
             mw::prefill_split_plan(pb, nl.data(), pl.data(), shape.num_q_heads, pcus, &pp);
             size_t most = 0;
             check(mw_prefill_workspace_size(&shape, pb, nl.data(), pl.data(), 0, &most) == MW_OK, "size call", it);
             check(pp.split_bytes <= most, "the size with no CU count covers the plan", it);
             check(pp.pieces >= 1 && pp.pieces <= mw::kPrefillMaxPieces, "pieces", it);
-            check(pp.pieces == 1 || (pp.waves == 4 && pp.piece_tiles >= mw::kPrefillMinPieceTiles), "cuts", it);
+            check(pp.pieces == 1 || (pp.dual && pp.waves == 4 && pp.piece_tiles >= mw::kPrefillMinPieceTiles), "cuts", it);
             for (int b = 0; b < pb; ++b)
-                for (int qb = 0; 32 * qb < nl[b] && pp.pieces > 1; ++qb) {
-                    const int nt = mw::prefill_block_tiles(pl[b], nl[b], qb);
+                for (int qb = 0; 128 * qb < nl[b] * group && pp.pieces > 1; ++qb) {
+                    const int nt = mw::prefill_block_tiles(pl[b], nl[b], qb, 128, group);
                     const int k = mw::prefill_pieces(nt, pp.piece_tiles, pp.pieces);
-                    // the last cut leaves the block's last two tiles (its diagonal) in the last piece
-                    check(k == 1 || (k - 1) * nt / k <= nt - 2, "cut before the diagonal", it);
-                    check(k == 1 || (k - 1) * nt / k <= (pl[b] + 32 * qb) / 64, "first tile of each piece visible", it);
+                    // equal pieces of two tiles or more, in order, up to the block's end
+                    for (int i = 0; i < k && k > 1; ++i)
+                        check((i + 1) * nt / k - i * nt / k >= 2, "a tile for each wave group of a piece", it);
+                    check(k * nt / k == nt, "pieces reach the block's end", it);
+                    // the last piece has three tiles or more, so every row of the block
+                    // (at most 128 positions) sees a key of every piece's first tile
+                    check(k == 1 || (k - 1) * nt / k <= nt - 3, "cut before the diagonal", it);
+                    check(k == 1 || (k - 1) * nt / k <= (pl[b] + 128 * qb / group) / 64, "first tile of each piece visible", it);
                 }
+            // the grid has a work-group for every block, in an order that it allows
+            int64_t blocks = 0, most_blocks = 0;
+            for (int b = 0; b < pb; ++b) {
+                const int64_t nb = (static_cast<int64_t>(nl[b]) * group + 32 * pp.waves - 1) / (32 * pp.waves);
+                blocks += nb;
+                most_blocks = std::max(most_blocks, nb);
+            }
+            check(pp.order >= 0 && pp.order <= 2 && (pp.order != 2 || (pb > 1 && pb <= 64)), "order", it);
+            check(pp.order == 2 ? pp.gy == 1 && pp.gx == blocks * hkv
+                                : pp.gy == pb && pp.gx == (pp.order == 1 ? (most_blocks + 1) / 2 : most_blocks) * hkv,
+                  "grid covers the blocks", it);
+            check(pp.big_units >= 0 && pp.big_units <= pp.gx && pp.big_units % hkv == 0 &&
+                      (pp.big_units == 0 || (pp.waves == 8 && pp.gy == 1 && !pp.dual)), "units of the mixed launch", it);
         }
         mw_kv_pool_destroy(pool);
     }
+}
+
+// The order over a batch: the counts that the kernel's search adds up against a
+// count block by block, and the blocks it gives work-groups 0, 1, ..: every block
+// once, no lighter one before a heavier one.  (The search is restated; sequences
+// take the place of lanes.)
+void batch_order() {
+    for (int it = 0; it < 300; ++it) {
+        const int batch = uniform(2, 64), group = uniform(1, 40), rows = uniform(0, 1) ? 128 : 256;
+        std::vector<int> n(batch), r(batch), nqb(batch);
+        std::vector<std::vector<int>> taken(batch);
+        int blocks = 0;
+        for (int b = 0; b < batch; ++b) {
+            n[b] = uniform(0, 5) == 0 ? 0 : uniform(1, it % 3 ? 100 : 2000);
+            r[b] = uniform(0, 3) == 0 ? 0 : uniform(0, 5000);
+            if (b > 0 && uniform(0, 4) == 0) n[b] = n[b - 1], r[b] = r[b - 1];
+            nqb[b] = (n[b] * group + rows - 1) / rows;
+            taken[b].assign(nqb[b], 0);
+            blocks += nqb[b];
+        }
+        const auto at_least = [&](int b, int t) { return mw::prefill_blocks_at_least(nqb[b], n[b], r[b], group, rows, t); };
+        const auto total = [&](int t) {
+            int s = 0;
+            for (int b = 0; b < batch; ++b) s += at_least(b, t);
+            return s;
+        };
+        for (int b = 0; b < batch; ++b)
+            for (int t = 1; t < 120; ++t) {
+                int count = 0;
+                for (int q = 0; q < nqb[b]; ++q) count += mw::prefill_block_tiles(r[b], n[b], q, rows, group) >= t;
+                check(at_least(b, t) == count, "blocks of t tiles or more", it);
+            }
+        int last_tiles = INT32_MAX;
+        for (int x = 0; x < blocks; ++x) {
+            int j = x, t = 1, step = 1;
+            while (total(t + step) > j) step <<= 1;
+            for (; step > 0; step >>= 1)
+                if (total(t + step) > j) t += step;
+            j -= total(t + 1);
+            bool found = false;
+            for (int b = 0, incl = 0; b < batch && !found; ++b) {
+                const int above = at_least(b, t + 1), same = at_least(b, t) - above;
+                incl += same;
+                if (j < incl - same || j >= incl) continue;
+                const int blk = nqb[b] - above - 1 + incl - same - j;
+                found = blk >= 0 && blk < nqb[b] && taken[b][blk]++ == 0;
+                const int tiles = found ? mw::prefill_block_tiles(r[b], n[b], blk, rows, group) : 0;
+                check(found && tiles == t && tiles <= last_tiles, "a block of its own, none lighter before", it);
+                last_tiles = tiles;
+            }
+            check(found, "a block for every work-group", it);
+        }
+    }
+    // the batches of the GPU test of this order are planned in it
+    for (int batch : {2, 63, 64, 65})
+        for (int cus : {8, 256}) {
+            std::vector<int32_t> n(batch), r(batch);
+            for (int b = 0; b < batch; ++b) r[b] = 53 * b % 1201, n[b] = 1 + 29 * b % 97;
+            r[0] = 300, n[0] = 700;
+            if (batch > 2) {
+                n[3] = n[batch - 1] = 0;
+                for (int b = 10; b < 20; ++b) r[b] = 600, n[b] = 33;
+            }
+            mw::PrefillPlan p{};
+            p.hkv = 2, p.group = 4;
+            mw::prefill_split_plan(batch, n.data(), r.data(), 8, cus, &p);
+            check((p.order == 2) == (batch <= 64), "the order test's batches are ordered", batch);
+        }
 }
 
 // A prefill workspace short of the plan's pieces: fewer pieces that fit, or none;
@@ -494,6 +580,7 @@ void estimator() {
 
 int main() {
     planners();
+    batch_order();
     short_workspaces();
     padding();
     prefill_sizes();

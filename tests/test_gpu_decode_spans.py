@@ -54,8 +54,8 @@ def test_decode_shares_across_segments(lo, hi, batch, cus):
     _check(6, 2, [int(x) for x in rng.integers(lo, hi + 1, batch)], cus, 60 + batch, q_scale=4.0)
 
 
-# one sequence cut into 137 pieces on the whole GPU (three blocks of 64 in the
-# merge's lanes), for every number of waves per head and heads per wave
+# one sequence cut into 244 pieces of 18 pages on the whole GPU (four blocks of 64
+# in the merge's lanes), for every number of waves per head and heads per wave
 @pytest.mark.parametrize("group", [1, 2, 3, 4, 5, 8, 9, 16])
 def test_decode_many_pieces(group):
     _check(group, 1, [70001], 0, 80 + group, q_scale=4.0)

@@ -99,15 +99,16 @@ def test_prefill_shared_keys(r, n, hq, hkv):
 
 # batches at the limit of the ordering over the whole batch (64 sequences) and
 # past it, with empty sequences, equal ones and one much longer than the rest
-@pytest.mark.parametrize("batch", [2, 64, 65])
+# (the host check of the launch planners, batch_order, holds that these very
+# batches are planned in that order, on 8 CUs as on 256, up to 64 sequences)
+@pytest.mark.parametrize("batch", [2, 63, 64, 65])
 @pytest.mark.parametrize("cus", [0, 8])
 def test_prefill_batch_order(batch, cus):
-    rng = np.random.default_rng(batch)
-    seqs = [(int(rng.integers(0, 90)), int(rng.integers(1, 40))) for _ in range(batch)]
+    seqs = [(53 * b % 1201, 1 + 29 * b % 97) for b in range(batch)]
     seqs[0] = (300, 700)
     if batch > 2:
-        seqs[3], seqs[batch - 1] = (5, 0), (17, 0)
-        seqs[10:20] = [(40, 33)] * 10
+        seqs[3], seqs[batch - 1] = (seqs[3][0], 0), (seqs[-1][0], 0)
+        seqs[10:20] = [(600, 33)] * 10
     say(f"prefill batch order {batch} sequences on {cus or 'all'} CUs")
     _run(8, 2, seqs, cus, 77)
 
