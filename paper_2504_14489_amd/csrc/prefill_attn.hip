@@ -164,11 +164,10 @@ k_prefill_merge(const float *__restrict__ ws_o, const float2 *__restrict__ ws_ml
 constexpr int kMaxSorted = 64;
 
 // The work-groups of one way to launch a call, from its lengths: `n` of them in
-// a grid of `grid` (the rest find no block), which run `blocks` query blocks of
-// `tiles` key tiles in all; tiles of the longest, of the lightest and of the last
-// sequence's longest.
+// a grid of `grid` (the rest find no block), of `tiles` key tiles in all; tiles of
+// the longest, of the lightest and of the last sequence's longest.
 struct Jobs {
-    int64_t n = 0, grid = 0, blocks = 0;
+    int64_t n = 0, grid = 0;
     double tiles = 0, longest = 0, lightest = 1e30, last = 0;
 };
 
@@ -180,15 +179,14 @@ struct Jobs {
 struct BodyCost {
     double around_alone, per_alone, around, per, empty, search, end_lightest, end_round, spread, end_last, late;
 };
-// Fitted by least squares of the log error to 2061 calls (1 to 16 sequences of 1
+// Fitted by least squares of the log error to 3261 calls (1 to 16 sequences of 1
 // to 4096 new tokens over 0 to 28672, groups of 1 to 16, 32 to 256 CUs, each
-// body, order and number of pieces measured on each: 15406 launches, 2%, 3% and
-// 5% off in the median). The cheapest by these is 2% slower than the fastest
+// body, order and number of pieces measured on each: 22000 launches, 3%, 3% and
+// 5% off in the median).  The cheapest by these is 2% slower than the fastest
 // measured of each call (geometric mean, calls of 8 us and more); with the choice
-// by CU count and an earlier fit it was 7%, and 88 calls instead of 41 were more
-// than 2% slower than with the four-heads-a-block layout.
-constexpr BodyCost kCost4{4.4, 1.18, 4.5, 1.57, 0.8, 0.9, 0.19, 0.36, 0.0, 0.22, 1.0};    // 2 work-groups per CU
-constexpr BodyCost kCost8{6.1, 1.27, 4.7, 1.48, 3.7, 1.3, 0.04, 0.67, 0.03, 0.23, 2.5};
+// by CU count and an earlier fit it was 7%.
+constexpr BodyCost kCost4{4.4, 1.18, 4.2, 1.525, 0.8, 1.05, 0.215, 0.39, 0.0, 0.2, 1.5};    // 2 work-groups per CU
+constexpr BodyCost kCost8{6.0, 1.28, 5.1, 1.415, 2.8, 1.26, 0.09, 0.64, 0.0, 0.21, 2.9};
 constexpr BodyCost kCostDual{5.7, 0.69, 5.3, 0.845, 0.8, 1.15, 0.28, 0.60, 0.53, 0.10, 1.1};
 constexpr double kMergeUs = 5.5, kMergeBytesPerUs = 8.8e6;  // the second launch, and its partials' way out and back
 
@@ -201,19 +199,19 @@ double launch_us(const BodyCost &c, const Jobs &j, int64_t cus, int per_cu, bool
     const double empty = sorted ? 0.0 : c.empty * (j.grid - j.n) / slots;
     // the longest work-group, alone on its CU or beside the heaviest of those
     // that no longer find an empty CU
-    double us = c.around_alone * j.blocks / j.n + search + c.per_alone * j.longest;
+    double us = c.around_alone + search + c.per_alone * j.longest;
     if (j.n > cus) {
         if (per_cu == 2) {
             const double beside = std::max(j.lightest, j.longest - (j.longest - j.lightest) * cus / j.n);
             us = std::max(us, c.around + search + c.per * beside + c.per_alone * (j.longest - beside));
         }
         // the even share, and past one round what the last one leaves idle
-        double share = (c.around * j.blocks + search * j.n + c.per * j.tiles) / slots + empty;
+        double share = ((c.around + search) * j.n + c.per * j.tiles) / slots + empty;
         if (j.n > slots) {
             const double rounds = static_cast<double>(j.n) / slots;
             share += c.end_lightest * (c.around + c.per * j.lightest) +
                      c.end_round * (1.0 - c.spread * (j.longest - j.lightest) / j.longest) *
-                         (std::ceil(rounds) - rounds) * (c.around * j.blocks + c.per * j.tiles) / j.n;
+                         (std::ceil(rounds) - rounds) * (c.around + c.per * j.tiles / j.n);
             if (!sorted && !one_sequence) share += c.end_last * (c.around + c.per * (j.last - j.lightest));
         }
         us = std::max(us, share);
@@ -221,6 +219,18 @@ double launch_us(const BodyCost &c, const Jobs &j, int64_t cus, int per_cu, bool
         us += empty;
     }
     return us + (!sorted && j.grid > j.n && j.grid > slots ? c.late : 0.0);
+}
+
+// Time of a launch of 8-wave pairs (blocks nqb-1-i and i).  Taken only where they
+// are alike (to 12%) and fill the rounds of the CUs (to 5%): a pair then costs one
+// start instead of two (2048 tokens of 32/8 heads on 64 CUs 107.7 us, single blocks
+// 116.8; 4096 on 32 750 and 787), and elsewhere its length makes the last round
+// (4096 on 96, 2.7 rounds: 282 and 267).  With these constants the choice is 1%
+// slower than the fastest of the 169 measured calls that have such pairs.
+double pairs_us(const Jobs &j, int64_t cus) {
+    const int64_t rounds = (j.n + cus - 1) / cus;
+    if (j.n < cus || rounds * cus * 20 > j.n * 21 || j.longest - j.lightest > 0.12 * j.longest) return INFINITY;
+    return std::max(8.0 + 1.42 * j.longest, (8.0 * j.n + 1.42 * j.tiles) / cus);
 }
 
 // A call's work-groups on blocks of 256 rows, one each (one8) and two each, nqb-1-i
@@ -254,10 +264,7 @@ CallJobs count_jobs(int32_t batch, const int32_t *h_new_lens, const int32_t *h_p
         c.most8 = std::max(c.most8, n8);
         c.most4 = std::max(c.most4, n4);
     }
-    c.one8.blocks = c.two8.blocks = c.one8.n;
-    c.one4.blocks = c.one4.n;
     c.one8.grid = c.most8 * hkv * batch;
-    c.two8.grid = (c.most8 + 1) / 2 * hkv * batch;
     c.one4.grid = c.most4 * hkv * batch;
     return c;
 }
@@ -284,7 +291,7 @@ double choose_plain(const CallJobs &c, int64_t cus, bool allow_small, PrefillPla
     };
     const bool one = p->batch == 1;
     take(launch_us(kCost8, c.one8, cus, 1, false, one), 8, kPerSequence);
-    take(launch_us(kCost8, c.two8, cus, 1, false, one), 8, kPairs);
+    take(pairs_us(c.two8, cus), 8, kPairs);
     if (sortable(p->batch)) take(launch_us(kCost8, c.one8, cus, 1, true, one), 8, kSorted);
     if (!allow_small) return best;
     take(launch_us(kCost4, c.one4, cus, 2, false, one), 4, kPerSequence);
@@ -366,7 +373,6 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
         if (k > 1) {
             jk.n *= k;
             jk.grid *= k;
-            jk.blocks *= k;
             jk.longest = pt;
             jk.lightest = 0.5 * pt;
             jk.last = std::min(jk.last, jk.longest);

@@ -208,6 +208,20 @@ void batch_order() {
             mw::prefill_split_plan(batch, n.data(), r.data(), 8, cus, &p);
             check((p.order == 2) == (batch <= 64), "the order test's batches are ordered", batch);
         }
+    // heavy-light pairs where they are alike and fill the rounds, and only there
+    const struct { int hq, hkv, cus; std::vector<int32_t> n, r; bool pairs; } calls[] = {
+        {32, 8, 64, {2048}, {0}, true},        {32, 8, 32, {1024}, {0}, true},
+        {32, 8, 32, {4096}, {0}, true},        {32, 8, 64, {4096}, {0}, true},
+        {32, 8, 128, {4096}, {0}, true},       {32, 8, 256, {4096}, {0}, true},
+        {32, 8, 96, {4096}, {0}, false},       {32, 8, 192, {4096}, {0}, false},
+        {32, 8, 64, {4096, 1024}, {0, 0}, false},
+    };
+    for (const auto &c : calls) {
+        mw::PrefillPlan p{};
+        p.hkv = c.hkv, p.group = c.hq / c.hkv;
+        mw::prefill_split_plan(static_cast<int>(c.n.size()), c.n.data(), c.r.data(), 8, c.cus, &p);
+        check((p.order == 1) == c.pairs, "pairs where they fill the rounds", c.cus);
+    }
 }
 
 // A prefill workspace short of the plan's pieces: fewer pieces that fit, or none;
