@@ -24,11 +24,11 @@
 // alternate tiles, each with its own buffers; and 4 waves on 128 rows, two
 // work-groups per CU.  The first needs the fewest K/V loads per flop.  The
 // second halves a block's time when there are too few blocks for the CUs: a
-// 4-wave work-group alone on its CU takes 1.4 us per tile whether or not
-// another one shares the CU's matrix cores, so the longest block of a
-// 2048-token prompt (32 tiles) bounded the launch at 46 us of a 54 us call; dual
-// blocks take 1.62 us per two tiles (1325 TFLOP/s over 256 CUs, the rate of a
-// 16384^3 library product) and the call 46 us.  The third keeps the plain
+// 4-wave work-group takes 1.2 us per tile alone on its CU and 1.5 beside another,
+// so the longest block of a 2048-token prompt (32 tiles) bounded the launch at
+// 46 us of a 54 us call; a dual one takes 0.7 us per tile on few CUs and 0.85 on
+// all (1.7 us for the two groups' tiles, 1270 TFLOP/s over 256 CUs, near the 1337
+// of a 16384^3 library product) and the call 46 us.  The third keeps the plain
 // entry point's results the same bits on any CU count (the groups' merge of
 // the second reorders sums).
 // Key tiles of 64 keys = 4 pages go from HBM straight into LDS with the direct
@@ -45,8 +45,8 @@
 //                            taken straight from the S^T accumulators as bf16
 // Online softmax in base 2 (scores scaled by scale*log2 e inside one FMA); the
 // causal mask is applied only on tiles that cross the diagonal; row sums are
-// taken in fp32 over the probabilities before they are rounded to bf16 for PV.  The running
-// maximum moves only when a column's tile maximum exceeds it by more than 2^8
+// taken in fp32 over the probabilities before they are rounded to bf16 for PV.
+// The running maximum moves only when a column's tile maximum exceeds it by more than 2^8
 // (O and l are then rescaled); O / l does not depend on the reference maximum.
 // O is staged through LDS so that each store writes whole 256-byte rows.
 // Causal position: query row i of a sequence with prefix r sees keys
