@@ -164,73 +164,91 @@ k_prefill_merge(const float *__restrict__ ws_o, const float2 *__restrict__ ws_ml
 constexpr int kMaxSorted = 64;
 
 // The work-groups of one way to launch a call, from its lengths: `n` of them in
-// a grid of `grid` (the rest find no block), of `tiles` key tiles in all; tiles of
-// the longest, of the lightest and of the last sequence's longest.
+// a grid of `grid`, or `sorted_grid` in length order (the rest find no work), of
+// `tiles` key tiles in all; tiles of the longest, of the lightest and of the last
+// sequence's longest.
 struct Jobs {
-    int64_t n = 0, grid = 0;
+    int64_t n = 0, grid = 0, sorted_grid = 0;
     double tiles = 0, longest = 0, lightest = 1e30, last = 0;
 };
 
 // What a work-group takes (us): around its tiles and per tile, alone on its CU
-// and on a full chip; to find its block in a batch in length order; a work-group
-// without a block; and how a launch of more work-groups than slots ends (shares
-// of the lightest one, of the last round's idle part, of how much the last
-// sequence's longest block exceeds the lightest).
+// and on a full partition, on 256 busy CUs; `clock`: the share of the time per
+// tile that the clock takes off it as fewer CUs are busy; to find its block in a
+// batch in length order; a work-group without work.  How a launch of more
+// work-groups than slots ends: shares of the lightest one (end_lightest), of the
+// last round's idle part, in lightest (end_round) and in what the mean has more
+// (end_mean), of how much the last sequence's longest block exceeds the lightest
+// (end_last); `uneven`: the work-groups go to the 32 groups of CUs (8 dies, 4
+// each) in turn, not to the first free one, so that with the heaviest first the
+// first group gets 16 x (longest - lightest) / cus more tiles a CU than the mean,
+// and this is the share of twice that which shows (`uneven_batch`: of sequences
+// one after the other).
 struct BodyCost {
-    double around_alone, per_alone, around, per, empty, search, end_lightest, end_round, spread, end_last, late;
+    double around_alone, per_alone, around, per, clock, empty, search, end_lightest, end_round, end_mean, end_last, late,
+        uneven, uneven_batch;
 };
-// Fitted by least squares of the log error to 3261 calls (1 to 16 sequences of 1
-// to 4096 new tokens over 0 to 28672, groups of 1 to 16, 32 to 256 CUs, each
-// body, order and number of pieces measured on each: 22000 launches, 3%, 3% and
-// 5% off in the median).  The cheapest by these is 2% slower than the fastest
-// measured of each call (geometric mean, calls of 8 us and more); with the choice
-// by CU count and an earlier fit it was 7%.
-constexpr BodyCost kCost4{4.4, 1.18, 4.2, 1.525, 0.8, 1.05, 0.215, 0.39, 0.0, 0.2, 1.5};    // 2 work-groups per CU
-constexpr BodyCost kCost8{6.0, 1.28, 5.1, 1.415, 2.8, 1.26, 0.09, 0.64, 0.0, 0.21, 2.9};
-constexpr BodyCost kCostDual{5.7, 0.69, 5.3, 0.845, 0.8, 1.15, 0.28, 0.60, 0.53, 0.10, 1.1};
-constexpr double kMergeUs = 5.5, kMergeBytesPerUs = 8.8e6;  // the second launch, and its partials' way out and back
+// Fitted by least squares of the log error to 5000 calls (1 to 16 sequences of 1
+// to 8192 new tokens over 0 to 131072, groups of 1 to 16, 32 to 256 CUs, each
+// body, order and number of pieces measured on each: 57000 launches, 4%, 4% and
+// 6% off in the median).  The cheapest by these is 1.8% slower than the fastest
+// measured of each call (geometric mean, calls of 8 us and more).  Fitted to
+// prefixes up to 28672 only, without the clock, the empty work-groups' places and
+// the uneven groups it was 2.6%, and 2048 tokens over 16384 on 192 CUs took 734
+// us, now 615.
+constexpr BodyCost kCost4{4.5, 1.285, 4.25, 1.6, 0.144, 1.04, 1.03, 0.326, 0.229, 0.325, 0.234, 0.17, 0.39, 0.04};    // 2 work-groups per CU
+constexpr BodyCost kCost8{6.2, 1.48, 5.5, 1.49, 0.188, 1.6, 1.1, 0.01, 0.8, 0.0, 0.18, 0.04, 0.57, 0.635};
+constexpr BodyCost kCostDual{5.55, 0.804, 5.8, 0.838, 0.215, 1.6, 1.56, 0.0, 0.723, 0.253, 0.0, 0.48, 0.15, 0.6};
+constexpr double kMergeUs = 5.6, kMergeBytesPerUs = 8.7e6;  // the second launch, and its partials' way out and back
+
+double at_clock(double clock, int64_t busy) {
+    return 1.0 - clock * (1.0 - static_cast<double>(std::min<int64_t>(busy, 256)) / 256);
+}
 
 // Time of a launch (us, without what is common to all), for CUs that hold
-// per_cu work-groups each.
+// per_cu work-groups each.  Work-groups without work take a place all the same:
+// 62 work-groups among 76 on 64 CUs take two rounds (554 us; in length order,
+// which leaves the empty ones out, 292).
 double launch_us(const BodyCost &c, const Jobs &j, int64_t cus, int per_cu, bool sorted, bool one_sequence) {
     if (j.n == 0) return 0.0;
-    const int64_t slots = per_cu * cus;
+    const int64_t slots = per_cu * cus, grid = sorted ? j.sorted_grid : j.grid;
     const double search = sorted ? c.search : 0.0;
-    const double empty = sorted ? 0.0 : c.empty * (j.grid - j.n) / slots;
+    const double empty = c.empty * (grid - j.n) / slots;
+    const double full = c.per * at_clock(c.clock, cus), alone = c.per_alone * at_clock(c.clock, std::min(j.n, cus));
     // the longest work-group, alone on its CU or beside the heaviest of those
     // that no longer find an empty CU
-    double us = c.around_alone + search + c.per_alone * j.longest;
-    if (j.n > cus) {
-        if (per_cu == 2) {
-            const double beside = std::max(j.lightest, j.longest - (j.longest - j.lightest) * cus / j.n);
-            us = std::max(us, c.around + search + c.per * beside + c.per_alone * (j.longest - beside));
-        }
-        // the even share, and past one round what the last one leaves idle
-        double share = ((c.around + search) * j.n + c.per * j.tiles) / slots + empty;
-        if (j.n > slots) {
-            const double rounds = static_cast<double>(j.n) / slots;
-            share += c.end_lightest * (c.around + c.per * j.lightest) +
-                     c.end_round * (1.0 - c.spread * (j.longest - j.lightest) / j.longest) *
-                         (std::ceil(rounds) - rounds) * (c.around + c.per * j.tiles / j.n);
-            if (!sorted && !one_sequence) share += c.end_last * (c.around + c.per * (j.last - j.lightest));
-        }
-        us = std::max(us, share);
-    } else {
-        us += empty;
+    double us = c.around_alone + search + alone * j.longest;
+    if (grid <= cus) return us + empty;
+    if (per_cu == 2 && j.n > cus) {
+        const double beside = std::max(j.lightest, j.longest - (j.longest - j.lightest) * cus / j.n);
+        us = std::max(us, c.around + search + full * beside + alone * (j.longest - beside));
     }
-    return us + (!sorted && j.grid > j.n && j.grid > slots ? c.late : 0.0);
+    // the even share, and past one round what the last one leaves idle
+    double share = ((c.around + search) * j.n + full * j.tiles) / slots + empty;
+    if (grid > slots) {
+        const double lightest = c.around + full * j.lightest, spread = full * (j.longest - j.lightest);
+        const double idle = std::clamp(std::ceil(static_cast<double>(grid) / slots) - static_cast<double>(j.n) / slots, 0.0, 1.0);
+        const bool batch_order = !sorted && !one_sequence;
+        share += c.end_lightest * lightest +
+                 idle * (c.end_round * lightest + c.end_mean * full * (j.tiles / j.n - j.lightest)) +
+                 (batch_order ? c.uneven_batch : c.uneven) * spread * 32 / slots;
+        if (batch_order) share += c.end_last * (c.around + full * (j.last - j.lightest));
+    }
+    return std::max(us, share) + (grid > j.n && grid > slots ? c.late : 0.0);
 }
 
 // Time of a launch of 8-wave pairs (blocks nqb-1-i and i).  Taken only where they
-// are alike (to 12%) and fill the rounds of the CUs (to 5%): a pair then costs one
-// start instead of two (2048 tokens of 32/8 heads on 64 CUs 107.7 us, single blocks
-// 116.8; 4096 on 32 750 and 787), and elsewhere its length makes the last round
-// (4096 on 96, 2.7 rounds: 282 and 267).  With these constants the choice is 1%
-// slower than the fastest of the 169 measured calls that have such pairs.
+// are alike (to 12%) and fill the rounds of the CUs (to 5%): every CU then gets the
+// same, where single blocks go to the CUs in turn, heaviest first (2048 tokens of
+// 32/8 heads on 64 CUs 107.7 us, single blocks 116.8; 4096 on 32 750 and 787);
+// elsewhere a pair's length makes the last round (4096 on 96, 2.7 rounds: 282 and
+// 267).  With these constants the choice is 0.8% slower than the faster one on
+// the 273 measured calls that have such pairs.
 double pairs_us(const Jobs &j, int64_t cus) {
     const int64_t rounds = (j.n + cus - 1) / cus;
     if (j.n < cus || rounds * cus * 20 > j.n * 21 || j.longest - j.lightest > 0.12 * j.longest) return INFINITY;
-    return std::max(8.0 + 1.42 * j.longest, (8.0 * j.n + 1.42 * j.tiles) / cus);
+    const double per = 1.46 * at_clock(kCost8.clock, cus);
+    return std::max(11.0 + per * j.longest, (11.0 * j.n + per * j.tiles) / cus);
 }
 
 // A call's work-groups on blocks of 256 rows, one each (one8) and two each, nqb-1-i
@@ -266,6 +284,8 @@ CallJobs count_jobs(int32_t batch, const int32_t *h_new_lens, const int32_t *h_p
     }
     c.one8.grid = c.most8 * hkv * batch;
     c.one4.grid = c.most4 * hkv * batch;
+    c.one8.sorted_grid = c.one8.n;
+    c.one4.sorted_grid = c.one4.n;
     return c;
 }
 
@@ -301,15 +321,16 @@ double choose_plain(const CallJobs &c, int64_t cus, bool allow_small, PrefillPla
 
 // Units (block, kv head) that a call of 256-row blocks on `cus` CUs runs as such
 // when the rest, its last and partial round, goes to dual blocks; 0: not such a
-// call.  Blocks taken longest first fill CUs evenly when they differ much in
-// length (a prompt without a prefix), so only calls whose lightest block has at
-// least half the tiles of the heaviest are treated.  There the last round costs a
-// whole block's time for any fraction f of a round; as dual blocks it costs a
-// little over half a block's while f <= 1/2.  Simulated over 2.3 to 5.3 rounds the
-// launch gets 5-17% shorter, and past f = 1/2 longer.  Measured: the 70B layer's
-// 2048-token chunk over 6144 cached tokens on 96 CUs (5.33 rounds) next to its
-// decode, 958 -> 911 us a step.
-int64_t big_units(const CallJobs &c, int64_t cus, const PrefillPlan &p) {
+// call, which takes `plain` us as one launch of one body.  Blocks taken longest
+// first fill CUs evenly when they differ much in length (a prompt without a
+// prefix), so only calls whose lightest block has at least half the tiles of the
+// heaviest are treated.  There the last round costs a whole block's time for any
+// fraction f of a round; as dual blocks it costs a little over half a block's while
+// f <= 1/2.  Simulated over 2.3 to 5.3 rounds the launch gets 5-17% shorter, and
+// past f = 1/2 longer.  Measured: the 70B layer's 2048-token chunk over 6144 cached
+// tokens on 96 CUs (5.33 rounds) next to its decode, 958 -> 911 us a step; on blocks
+// of 2 tiles, where starts are all, 4-wave blocks 13.8 us and this 20.8.
+int64_t big_units(const CallJobs &c, int64_t cus, const PrefillPlan &p, double plain) {
     const int64_t units = c.one8.n, whole = units / cus * cus;
     if (whole < 2 * cus || whole == units || 2 * (units - whole) > cus) return 0;
     if (2 * c.one8.lightest < c.one8.longest) return 0;
@@ -317,7 +338,11 @@ int64_t big_units(const CallJobs &c, int64_t cus, const PrefillPlan &p) {
     if (p.batch > 1 && (!sortable(p.batch) || launch_us(kCost8, c.one8, cus, 1, true, false) >
                                                   launch_us(kCost8, c.one8, cus, 1, false, false)))
         return 0;
-    return whole / p.hkv * p.hkv;
+    const double rest = c.one8.lightest + (c.one8.longest - c.one8.lightest) * (units - whole) / units;
+    const double us = whole / cus * (kCost8.around + (p.batch > 1 ? kCost8.search : 0.0) +
+                                     kCost8.per * at_clock(kCost8.clock, cus) * c.one8.tiles / units) +
+                      kCostDual.around_alone + kCostDual.per_alone * at_clock(kCostDual.clock, cus) * rest;
+    return us < plain ? whole / p.hkv * p.hkv : 0;
 }
 
 }  // namespace
@@ -350,12 +375,12 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
         p->split_bytes = bytes_for(p->pieces);
         return;
     }
-    p->big_units = big_units(c, cus, *p);
+    const double plain = choose_plain(c, cus, true, p);
+    p->big_units = big_units(c, cus, *p, plain);
     if (p->big_units > 0) {
         set_launch(p, 8, batch == 1 ? kPerSequence : kSorted, c);
         return;
     }
-    const double plain = choose_plain(c, cus, true, p);
     // Dual blocks, whole or in pieces.  Only launches of few blocks are cut: two
     // blocks per CU and more even out by themselves.  Two kinds always are, as
     // every caller's workspace provides for: fewer than two blocks per CU of 96
@@ -365,19 +390,40 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     const bool cuttable = c.two8.n < cus && j.n < 2 * cus && bytes_for(2) <= workspace_bytes;
     const bool must_cut = cuttable && (max_nt >= 96 || (4 * j.n <= cus && max_nt >= 10));
     double best = must_cut ? INFINITY : plain;
+    // the blocks' tiles and how many blocks have them, from up to 64 blocks of a
+    // sequence, the lightest and the longest among them
+    std::vector<std::pair<int, double>> lengths;
+    for (int32_t b = 0; cuttable && b < batch; ++b) {
+        const int64_t n = h_new_lens[b], r = h_prefix_lens[b], nqb = (n * p->group + 127) / 128;
+        const int64_t taken = std::min<int64_t>(nqb, 64);
+        for (int64_t i = 0; i < taken; ++i) {
+            const int64_t q = taken > 1 ? i * (nqb - 1) / (taken - 1) : 0;
+            const int nt = prefill_block_tiles<int64_t>(r, n, q, 128, p->group);
+            if (lengths.empty() || lengths.back().first != nt) lengths.emplace_back(nt, 0.0);
+            lengths.back().second += static_cast<double>(nqb * p->hkv) / taken;
+        }
+    }
     for (int k = must_cut ? 2 : 1; k <= (cuttable ? kPrefillMaxPieces : 1); ++k) {
         const int pt = std::max(kPrefillMinPieceTiles, (max_nt + k - 1) / k);
         if (k > 1 && (pt >= max_nt || bytes_for(prefill_pieces(max_nt, pt, kPrefillMaxPieces)) > workspace_bytes)) break;
         Jobs jk = j;
         double merge = 0.0;
         if (k > 1) {
-            jk.n *= k;
             jk.grid *= k;
-            jk.longest = pt;
-            jk.lightest = 0.5 * pt;
-            jk.last = std::min(jk.last, jk.longest);
+            jk.sorted_grid *= k;
+            jk.longest = 0;
+            jk.lightest = max_nt;
+            double found = 0.0;
+            for (const auto &[nt, blocks] : lengths) {
+                const int np = prefill_pieces(nt, pt, k);
+                found += np * blocks;
+                jk.longest = std::max<double>(jk.longest, (nt + np - 1) / np);
+                jk.lightest = std::min<double>(jk.lightest, nt / np);
+            }
+            jk.n = static_cast<int64_t>(found + 0.5);
+            jk.last = std::min(j.last, jk.longest);
             const double cut = std::min(1.0, static_cast<double>(max_nt - pt) / (max_nt - min_nt + 1));
-            merge = kMergeUs + cut * 2.0 * bytes_for(k) / kMergeBytesPerUs;
+            merge = kMergeUs + cut * 2.0 * bytes_for(prefill_pieces(max_nt, pt, k)) / kMergeBytesPerUs;
         }
         for (int sorted = 0; sorted <= (sortable(batch) ? 1 : 0); ++sorted) {
             const double us = launch_us(kCostDual, jk, cus, 1, sorted != 0, batch == 1) + merge;

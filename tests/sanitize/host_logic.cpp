@@ -199,7 +199,9 @@ void batch_order() {
             std::vector<int32_t> n(batch), r(batch);
             for (int b = 0; b < batch; ++b) r[b] = 53 * b % 1201, n[b] = 1 + 29 * b % 97;
             r[0] = 300, n[0] = 700;
-            if (batch > 2) {
+            if (batch == 2) {
+                r = {2000, 1900}, n = {759, 61};
+            } else {
                 n[3] = n[batch - 1] = 0;
                 for (int b = 10; b < 20; ++b) r[b] = 600, n[b] = 33;
             }
@@ -222,6 +224,23 @@ void batch_order() {
         mw::prefill_split_plan(static_cast<int>(c.n.size()), c.n.data(), c.r.data(), 8, c.cus, &p);
         check((p.order == 1) == c.pairs, "pairs where they fill the rounds", c.cus);
     }
+    // equal long blocks just past a round of 256-row ones: dual blocks, whose rounds
+    // are half as long; pieces that fill the CUs' rounds; and two sequences of
+    // which the shorter one's missing blocks would take the places of a second round
+    // (in length order they are left out)
+    mw::PrefillPlan p{};
+    p.hkv = 8, p.group = 4;
+    const int32_t n[2] = {2048, 256}, r[2] = {16384, 131072};
+    for (int cus : {192, 224}) {
+        mw::prefill_split_plan(1, n, r, 32, cus, &p);
+        check(p.dual && p.pieces == 1, "dual blocks past a round", cus);
+    }
+    mw::prefill_split_plan(1, n + 1, r + 1, 32, 160, &p);
+    check(p.dual && p.pieces == 5, "pieces in whole rounds", p.pieces);
+    p.hkv = 1, p.group = 16;
+    const int32_t n2[2] = {89, 146}, r2[2] = {51576, 53735};
+    mw::prefill_split_plan(2, n2, r2, 16, 64, &p);
+    check(p.dual && (p.order == 2 || p.gx * p.gy * p.pieces <= 64), "places of empty work-groups", p.pieces);
 }
 
 // A prefill workspace short of the plan's pieces: fewer pieces that fit, or none;

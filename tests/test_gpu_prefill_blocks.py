@@ -106,7 +106,9 @@ def test_prefill_shared_keys(r, n, hq, hkv):
 def test_prefill_batch_order(batch, cus):
     seqs = [(53 * b % 1201, 1 + 29 * b % 97) for b in range(batch)]
     seqs[0] = (300, 700)
-    if batch > 2:
+    if batch == 2:
+        seqs = [(2000, 759), (1900, 61)]
+    else:
         seqs[3], seqs[batch - 1] = (seqs[3][0], 0), (seqs[-1][0], 0)
         seqs[10:20] = [(600, 33)] * 10
     say(f"prefill batch order {batch} sequences on {cus or 'all'} CUs")
