@@ -124,8 +124,9 @@ bool decode_terms(int32_t batch, const int32_t *lens, double out[4]) {
 // factor: the latest CU's finishing time over the time of the same work spread
 // evenly over the CUs.  It has the steps of a launch (rounds of work-groups,
 // the longest one), not the library's choice of bodies, orders and pieces, which
-// follows measured times call by call (prefill_attn.hip).  The work-groups are taken in dispatch order (grid x
-// fastest, then the sequence) and each goes to the CU slot that frees first,
+// follows measured times call by call (prefill_attn.hip).  The work-groups are
+// taken in dispatch order (grid x fastest, then the sequence) and each goes to the
+// CU slot that frees first,
 // all CUs' first slots before any second one; a work-group's work is its key
 // tiles (64 keys each), summed over the blocks it takes.  A CU that holds a
 // single work-group of a two-per-CU launch runs it at 0.9 of a shared CU's

@@ -52,8 +52,9 @@ __host__ __device__ inline int prefill_pieces(int nt, int piece_tiles, int max_p
     return k < 1 ? 1 : (k > max_pieces ? max_pieces : k);
 }
 // Key tiles (64 keys) of query block q of a sequence with prefix r and n new
-// tokens: blocks of `block_rows` rows of its n x group queries.  T: the type of the row counts; 32 bits hold those of a call that
-// fits the device's memory, but not of every length a caller may ask a size for.
+// tokens: blocks of `block_rows` rows of its n x group queries.  T: the type of
+// the row counts; 32 bits hold those of a call that fits the device's memory, but
+// not of every length a caller may ask a size for.
 template <class T = int>
 __host__ __device__ inline int prefill_block_tiles(T r, T n, T q, T block_rows, T group) {
     const T end = (q + 1) * block_rows < n * group ? (q + 1) * block_rows : n * group;

@@ -179,11 +179,11 @@ struct Jobs {
 // work-groups than slots ends: shares of the lightest one (end_lightest), of the
 // last round's idle part, in lightest (end_round) and in what the mean has more
 // (end_mean), of how much the last sequence's longest block exceeds the lightest
-// (end_last); `uneven`: the work-groups go to the 32 groups of CUs (8 dies, 4
-// each) in turn, not to the first free one, so that with the heaviest first the
-// first group gets 16 x (longest - lightest) / cus more tiles a CU than the mean,
-// and this is the share of twice that which shows (`uneven_batch`: of sequences
-// one after the other).
+// (end_last); `uneven`: by the times of launches of several rounds, work-groups go
+// to groups of CUs (8 dies, 4 groups each) in turn and not to the CU that is free
+// first, so that with the heaviest first the first group gets 16 x (longest -
+// lightest) / cus more tiles a CU than the mean; the share of twice that which
+// shows (`uneven_batch`: of sequences one after the other).
 struct BodyCost {
     double around_alone, per_alone, around, per, clock, empty, search, end_lightest, end_round, end_mean, end_last, late,
         uneven, uneven_batch;
@@ -239,7 +239,7 @@ double launch_us(const BodyCost &c, const Jobs &j, int64_t cus, int per_cu, bool
 
 // Time of a launch of 8-wave pairs (blocks nqb-1-i and i).  Taken only where they
 // are alike (to 12%) and fill the rounds of the CUs (to 5%): every CU then gets the
-// same, where single blocks go to the CUs in turn, heaviest first (2048 tokens of
+// same, where single blocks, heaviest first, leave uneven CUs (2048 tokens of
 // 32/8 heads on 64 CUs 107.7 us, single blocks 116.8; 4096 on 32 750 and 787);
 // elsewhere a pair's length makes the last round (4096 on 96, 2.7 rounds: 282 and
 // 267).  With these constants the choice is 0.8% slower than the faster one on

@@ -388,7 +388,7 @@ int dual_merge_clashes(bool ml_in_v, Ml ml_at, Stage stage_at) {
 
 void dual_merge() {
     check(dual_merge_clashes(false, mw::dual_ml, mw::dual_stage) == 0, "LDS regions of the dual merge", -1);
-    // the checker finds the words at the start of the V buffers and the rows
+    // the check finds the words at the start of the V buffers and the rows
     // 1 KiB behind them, whose last fp32 rows run over the end
     check(dual_merge_clashes(true, [](int, int row) { return 8 * row; }, [](int w) { return 1024 + 8192 * w; }) > 0,
           "a clash planted in the dual merge's regions", -1);
