@@ -391,16 +391,21 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
     const bool must_cut = cuttable && (max_nt >= 96 || (4 * j.n <= cus && max_nt >= 10));
     double best = must_cut ? INFINITY : plain;
     // the blocks' tiles and how many blocks have them, from up to 64 blocks of a
-    // sequence, the lightest and the longest among them
-    std::vector<std::pair<int, double>> lengths;
+    // sequence, the lightest and the longest among them.  512 hold every cuttable
+    // call of 256 CUs; what a larger one has beyond counts with the last
+    struct Length {
+        int tiles;
+        double blocks;
+    } lengths[512];
+    int kinds = 0;
     for (int32_t b = 0; cuttable && b < batch; ++b) {
         const int64_t n = h_new_lens[b], r = h_prefix_lens[b], nqb = (n * p->group + 127) / 128;
         const int64_t taken = std::min<int64_t>(nqb, 64);
         for (int64_t i = 0; i < taken; ++i) {
             const int64_t q = taken > 1 ? i * (nqb - 1) / (taken - 1) : 0;
             const int nt = prefill_block_tiles<int64_t>(r, n, q, 128, p->group);
-            if (lengths.empty() || lengths.back().first != nt) lengths.emplace_back(nt, 0.0);
-            lengths.back().second += static_cast<double>(nqb * p->hkv) / taken;
+            if (kinds == 0 || (lengths[kinds - 1].tiles != nt && kinds < 512)) lengths[kinds++] = {nt, 0.0};
+            lengths[kinds - 1].blocks += static_cast<double>(nqb * p->hkv) / taken;
         }
     }
     for (int k = must_cut ? 2 : 1; k <= (cuttable ? kPrefillMaxPieces : 1); ++k) {
@@ -414,9 +419,9 @@ void prefill_split_plan(int32_t batch, const int32_t *h_new_lens, const int32_t 
             jk.longest = 0;
             jk.lightest = max_nt;
             double found = 0.0;
-            for (const auto &[nt, blocks] : lengths) {
-                const int np = prefill_pieces(nt, pt, k);
-                found += np * blocks;
+            for (int i = 0; i < kinds; ++i) {
+                const int nt = lengths[i].tiles, np = prefill_pieces(nt, pt, k);
+                found += np * lengths[i].blocks;
                 jk.longest = std::max<double>(jk.longest, (nt + np - 1) / np);
                 jk.lightest = std::min<double>(jk.lightest, nt / np);
             }
